@@ -8,7 +8,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libbigcn.so")
 SOURCES = [os.path.join(HERE, "csrc", f)
-           for f in ("bigcn_kernels.hip", "bigcn_api.hip", "bigcn_backward.hip")]
+           for f in ("bigcn_kernels.hip", "bigcn_e2m1.hip", "bigcn_api.hip",
+                     "bigcn_backward.hip")]
 
 # -packed-fp32-ops keeps the compiler from emitting packed fp32 VALU ops in
 # the device code.  hipcc hands -Xclang options to the host pass as well,

@@ -111,15 +111,19 @@ struct ForwardLayout {
   int32_t dmax;
 };
 
-// Whether layer l's aggregation produces layer l+1's products in its
-// epilogue (see bigcn::FusedNext): both layers on the 8-bit path.
+// Whether layer l's aggregation produces layer l+1's input in its epilogue
+// (see bigcn::FusedNext): both layers on the 8-bit path; packed signs (kind 4)
+// if layer l+1's products come from the matrix-core GEMM (wide layers: forming 65-256 products of a row by bit
+// counts in the epilogue takes longer than the GEMM, which is bound by
+// writing them), else its products (kind 1).
 int fuse_kind(int64_t n, int64_t nnz, const bigcn_layer* layers, int32_t nl, int32_t l) {
   if (l + 1 >= nl || nnz == 0) return 0;
   const bigcn_layer& a = layers[l];
   const bigcn_layer& b = layers[l + 1];
   if (a.wbits_self != nullptr || b.wbits_self != nullptr) return 0;  // GraphSAGE layers
   if (!bigcn::q8_supported(n, a.d_out, a.d_in)) return 0;  // producer: 8-bit wave kernel
-  return bigcn::q8_supported(n, b.d_out, b.d_in) ? 1 : 0;
+  if (!bigcn::q8_supported(n, b.d_out, b.d_in)) return 0;
+  return bigcn::bgemm_q8_e2m1_supported(n, b.d_out, b.d_in) ? 4 : 1;
 }
 
 // Row stride (bytes of codes, or halves of exact products) of the 8-bit
@@ -540,6 +544,7 @@ bigcn_status bigcn_forward(int64_t n, int64_t nnz, const int64_t* rowptr,
   const float* hin = x;
   int64_t ldin = ldx;
   bool have_products = false;  // layer l's products already written by layer l-1
+  bool have_signs = false;     // or its packed signs and scale
   for (int32_t l = 0; l < n_layers; ++l) {
     const bigcn_layer& ly = layers[l];
     const bool last = l + 1 == n_layers;
@@ -549,7 +554,11 @@ bigcn_status bigcn_forward(int64_t n, int64_t nnz, const int64_t* rowptr,
     void* C16 = ws + L.off_C16[set];
     const bool q8 = bigcn::q8_supported(n, ly.d_out, ly.d_in);
     const IType ct = forward_itype(ly.d_in);
-    if (!have_products && q8 && ly.wbits_self == nullptr &&
+    if (have_signs) {
+      e = bigcn::launch_bgemm_q8(F, n, bigcn::sign_row_words(ly.d_in), ly.wbits, ly.d_out, ly.ldw,
+                                 ly.d_in, C8, q8_row(ly.d_out), C16, q8_row(ly.d_out), g, s);
+      if (e != hipSuccess) return BIGCN_EHIP;
+    } else if (!have_products && q8 && ly.wbits_self == nullptr &&
         bigcn::pack_bgemm_q8_supported(ly.d_in, ly.d_out, ldin)) {
       e = bigcn::launch_pack_bgemm_q8(hin, n, ly.d_in, ldin, l == 0 ? mu : nullptr,
                                       l == 0 ? rstd : nullptr, rowptr,
@@ -615,6 +624,8 @@ bigcn_status bigcn_forward(int64_t n, int64_t nnz, const int64_t* rowptr,
         fn.C16 = ws + L.off_C16[nset];
         fn.ldc16 = q8_row(nxt.d_out);
         fn.g = (float*)(ws + L.off_g[nset]);
+        fn.Fn = F;
+        fn.ldFn = bigcn::sign_row_words(nxt.d_in);
       }
       e = bigcn::launch_spmm_q8(n, nnz, rowptr, gcol, norm == BIGCN_NORM_MEAN, g, C8,
                                 q8_row(ly.d_out), C16, q8_row(ly.d_out), ly.d_in, ly.d_out,
@@ -626,7 +637,8 @@ bigcn_status bigcn_forward(int64_t n, int64_t nnz, const int64_t* rowptr,
                              hout, ldout, plan, wsp, s);
     }
     if (e != hipSuccess) return BIGCN_EHIP;
-    have_products = kind != 0;
+    have_products = kind == 1;
+    have_signs = kind == 4;
     hin = hout;
     ldin = ldout;
   }

@@ -200,7 +200,9 @@ __device__ inline float4_t load_partial(const float* p) {
 //            over c, then a butterfly: the order of the pack kernel), and its
 //            products against the next weights (in LDS) are written as 8-bit
 //            half-codes with the exact fallback, as k_bgemm_pop_q8 does.
-// With NX == 1 the output row is also written to out if out != nullptr.
+//   NX == 4: the next layer reads packed signs: the row's words (the ballots
+//            of NX == 1) and scale are written, no products are formed.
+// With NX == 1 or 4 the output row is also written to out if out != nullptr.
 struct NextLayer {
   int32_t dn;          // next layer's output width d'
   int8_t* C8;          // codes [n][ldc8]
@@ -217,6 +219,8 @@ struct NextLayer {
   const uint64_t* F;      // NX == 3: the layer's packed signs, row r at F + r ldF
   int64_t ldF;            // (r = slot[r] when slot is given)
   int32_t kin;            // NX == 3: the layer's input width
+  uint64_t* Fn;           // NX == 4: the next layer's packed signs [n][ldFn],
+  int64_t ldFn;           // ldFn <= NB words (pad words are written as zero)
 };
 
 // The next layer's weights as finish_row reads them.
@@ -266,6 +270,8 @@ inline FinishArgs finish_args(int mean, const float* g, int32_t d, const float* 
   nx.F = fn.F;
   nx.ldF = fn.ldF;
   nx.kin = fn.kin;
+  nx.Fn = fn.Fn;
+  nx.ldFn = fn.ldFn;
   fa.out = out;
   fa.ldo = ldo;
   fa.alpha = alpha;
@@ -332,11 +338,16 @@ __device__ inline void load_row_words(uint64_t (&fw)[NW], const uint64_t* __rest
   for (int w = 0; w < NW; ++w) fw[w] = w < kw ? row[w] : 0ull;
 }
 
-// Lane 0's v to *p, through a buffer of that size (no branch on the lane, see
-// finish_row).
+// Lane 0's v to *p, and lanes 0 .. n - 1's words to p[0 .. n), through
+// buffers of that size (no branch on the lane, see finish_row).
 __device__ inline void store_first(float* p, int lane, float v) {
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), raw_rsrc(p, 4u),
                                         lane * 4, 0, 0);
+}
+__device__ inline void store_words(uint64_t* p, uint32_t n, int lane, uint64_t v) {
+  typedef uint32_t uint2_b __attribute__((ext_vector_type(2)));
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2_b, v), raw_rsrc(p, n * 8u),
+                                        lane * 8, 0, 0);
 }
 
 template <int NX, int NB, int NBN, bool EPI_LDS>
@@ -408,14 +419,14 @@ __device__ inline void finish_row(int64_t r, int64_t deg, const float4_t acc,
   // those loops apart for the lanes on either side of it, and cross-lane
   // reads of the row window found lanes that had not moved on yet (after rows
   // without entries some rows were then never written).
-  if (NX != 1 || fa.out != nullptr) {
+  if ((NX != 1 && NX != 4) || fa.out != nullptr) {
     const __amdgpu_buffer_rsrc_t rso = raw_rsrc(fa.out + r * fa.ldo, (uint32_t)fa.d * 4u);
 #pragma unroll
     for (int c = 0; c < NB; ++c)
       __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v[c]), rso,
                                             (lane + 64 * c) * 4, 0, 0);
   }
-  if (NX != 1) return;
+  if (NX != 1 && NX != 4) return;
   // Next layer: signs (one ballot per 64 elements = one packed word) and
   // mean magnitude, exactly as the pack kernel forms them.
   uint64_t word[NB];
@@ -428,6 +439,15 @@ __device__ inline void finish_row(int64_t r, int64_t deg, const float4_t acc,
   l1 = wave_sum(l1);
   float sc = l1 / (float)fa.d;
   if (nx.sym) sc = sc * (deg > 0 ? 1.0f / sqrtf((float)deg) : 0.f);
+  if constexpr (NX == 4) {
+    uint64_t mine = word[0];  // lane w: word w
+#pragma unroll
+    for (int c = 1; c < NB; ++c)
+      if (lane == c) mine = word[c];
+    store_words(nx.Fn + dst * nx.ldFn, (uint32_t)nx.ldFn, lane, mine);
+    store_first(nx.g + dst, lane, sc);
+    return;
+  }
   const int kwn = (fa.d + 63) >> 6;  // <= NB
   const int Kn = fa.d;
   const int par = Kn & 1;
@@ -531,7 +551,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_fix_q8(
   if (NX == 1) load_next_weights<NB, NBN>(nr, fa.nx.dn, sBn, Bn, ldbn, fa.d, lane);
   // NX == 3: the self weights, NBN words by NB columns per lane, in LDS
   if (NX == 3) load_next_weights<NBN, NB>(nr, fa.d, sBn, Bn, ldbn, fa.nx.kin, lane);
-  constexpr bool kEpiLds = NX == 1 || NX == 3;  // where finish_row reads alpha / bias
+  constexpr bool kEpiLds = NX == 1 || NX == 3 || NX == 4;  // where finish_row reads alpha / bias
   if constexpr (kEpiLds) stage_epi(s_epi, fa);
   EpiRegs<NB> er = {};
   if constexpr (!kEpiLds) make_epi_regs<NB>(er, fa, lane);

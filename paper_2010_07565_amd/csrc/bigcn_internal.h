@@ -63,6 +63,13 @@ hipError_t launch_bgemm_q8(const uint64_t* F, int64_t M, int64_t ldf,
                            int8_t* C8, int64_t ldc8, void* C16, int64_t ldc16,
                            float* g, hipStream_t stream);
 
+// launch_bgemm_q8 on the matrix cores (e2m1 signs), the same results; taken
+// by launch_bgemm_q8 where it is supported.
+bool bgemm_q8_e2m1_supported(int64_t M, int32_t N, int32_t K);
+hipError_t launch_bgemm_q8_e2m1(const uint64_t* F, int64_t M, int64_t ldf, const uint64_t* B,
+                                int32_t N, int64_t ldb, int32_t K, int8_t* C8, int64_t ldc8,
+                                void* C16, int64_t ldc16, float* g, hipStream_t stream);
+
 // A next layer fused into the 8-bit aggregation's epilogue: the finished
 // output rows are binarised and multiplied with the next weights in place.
 //   kind 0: none (the output rows are written);
@@ -76,6 +83,8 @@ hipError_t launch_bgemm_q8(const uint64_t* F, int64_t M, int64_t ldf,
 //           aggregation's g and products use) and the self weights' packed
 //           W^T (wself [d][ldw_self], kin inputs) instead of read from Cself;
 //           see self_in_epilogue_supported.
+//   kind 4: the next layer's packed signs (Fn, rows of ldFn words) for
+//           launch_bgemm_q8.
 // g receives the next layer's per-node scale.
 struct FusedNext {
   int kind;
@@ -98,6 +107,8 @@ struct FusedNext {
   const uint64_t* wself;
   int64_t ldw_self;
   int32_t kin;
+  uint64_t* Fn;           // kind 4
+  int64_t ldFn;
 };
 // Layers whose self term kind 3 can form: the wide 8-bit aggregation (65-256
 // outputs) with the self weights' words per lane, ceil(kin / 64) times
@@ -143,6 +154,9 @@ hipError_t launch_spmm_q8(int64_t n, int64_t nnz, const int64_t* rowptr,
                           const float* bias, int relu, float* out, int64_t ldo,
                           const SpmmPlan& plan, void* workspace,
                           const FusedNext* next, hipStream_t stream);
+
+// Words of a packed sign row between fused layers (pad words zero).
+constexpr int64_t sign_row_words(int32_t K) { return K <= 128 ? 2 : 4; }
 
 // Source order of the forward pass (see bigcn_source_slots): slot[i] for
 // every node, colslot[e] = slot[colidx[e]]; workspace of SlotPlan::bytes.

@@ -1065,7 +1065,7 @@ __device__ inline void fma_n(float4_t& acc, float g, const float4_t& v) {
 // 4.11 ms against 3.81), else 6 (the odd-K self term spills at 8).
 template <int U, int NX, int NB, int NBN, int P>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
-    U == 8 && (NX == 1 || (NX == 3 && P == 0)) ? 8 : U == 16 ? 5 : 6))) void k_spmm_wave_q8(
+    U == 8 && (NX == 1 || NX == 4 || (NX == 3 && P == 0)) ? 8 : U == 16 ? 5 : 6))) void k_spmm_wave_q8(
     FinishArgs fa, int64_t n, int64_t nnz, const int64_t* __restrict__ rowptr,
     const int32_t* __restrict__ colidx, const float* __restrict__ g,
     const int8_t* __restrict__ C8, int64_t ldc8, const _Float16* __restrict__ C16,
@@ -1095,7 +1095,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
   // NX == 3: the self weights, NBN words by NB columns per lane, in LDS
   if (NX == 3) load_next_weights<NBN, NB>(nr, fa.d, sBn, Bn, ldbn, fa.nx.kin, lane);
   // where finish_row reads its arguments and alpha / bias (see EpiRegs)
-  constexpr bool kEpiLds = NX == 1 || NX == 3 || U == 16;
+  constexpr bool kEpiLds = NX == 1 || NX == 3 || NX == 4 || U == 16;
   if constexpr (kEpiLds) stage_epi(s_epi, fa);
   EpiRegs<NB> er = {};
   if constexpr (!kEpiLds) make_epi_regs<NB>(er, fa, lane);
@@ -1490,7 +1490,7 @@ struct NarrowEpi {
 };
 
 // A finished row in one slot: the same epilogue as finish_row (rescale,
-// bias, self term, activation), the output written or, for NX == 1, the
+// bias, self term, activation), the output written or, for NX == 1 or 4, the
 // next layer formed in place.  Its scale is the mean |value| summed in the
 // order of the pack kernel's wave reduction (lane c holds elements
 // 16c .. 16c + 15, one 16-lane row of that reduction: a balanced tree inside
@@ -1500,8 +1500,7 @@ struct NarrowEpi {
 template <int G, int CPL, int NX>
 __device__ inline void finish_slot(int64_t r, int64_t deg, int mean, const float (&sum)[CPL],
                                    const NarrowEpi& ep, int c, float* __restrict__ out,
-                                   int64_t ldo, const NextLayer& nx, int nbn,
-                                   const uint64_t* s_bn) {
+                                   int64_t ldo, const NextLayer& nx, const uint64_t* s_bn) {
   static_assert(CPL * G <= 64 && CPL <= 16 && CPL % 4 == 0, "narrow layout");
   const float rowfac = deg > 0 ? row_factor_deg(deg, mean) : 0.f;
   int64_t dst = r;  // row of the next products / self products
@@ -1535,7 +1534,7 @@ __device__ inline void finish_slot(int64_t r, int64_t deg, int mean, const float
       t += ok ? gi * sv[k] * (float)nx.Cself[dst * nx.ldself + CPL * c + k] : 0.f;
     v[k] = act(t, ep.relu);
   }
-  if (NX != 1 || out != nullptr) {
+  if ((NX != 1 && NX != 4) || out != nullptr) {
     float* o = out + r * ldo + CPL * c;
     if (ep.vec && ep.valid == (1u << CPL) - 1) {
 #pragma unroll
@@ -1551,7 +1550,7 @@ __device__ inline void finish_slot(int64_t r, int64_t deg, int mean, const float
         if ((ep.valid >> k) & 1) o[k] = v[k];
     }
   }
-  if (NX != 1) return;
+  if (NX != 1 && NX != 4) return;
   uint32_t m = 0;
   float a[16];
 #pragma unroll
@@ -1579,13 +1578,22 @@ __device__ inline void finish_slot(int64_t r, int64_t deg, int mean, const float
         mean == 0 ? rowfac : (deg > 0 ? 1.0f / sqrtf((float)deg) : 0.f);
     sc = sc * isd;
   }
+  if constexpr (NX == 4) {  // the next layer reads packed signs (ldFn = 2: one pad word)
+    if (c == 0) {
+      uint64_t* f = nx.Fn + dst * nx.ldFn;
+      f[0] = word;
+      f[1] = 0;
+      nx.g[dst] = sc;
+    }
+    return;
+  }
   const int Kn = ep.d;
   const int par = Kn & 1;
   for (int kq = c; kq < nx.dn; kq += G) {
     const uint64_t z = word ^ s_bn[kq];
     const int pc = __builtin_popcount((uint32_t)z) + __builtin_popcount((uint32_t)(z >> 32));
     const int code = ((Kn - 2 * pc) - par) >> 1;
-    nx.C8[dst * nx.ldc8 + nbn * (kq & 63) + (kq >> 6)] = (int8_t)code;
+    nx.C8[dst * nx.ldc8 + kq] = (int8_t)code;
   }
   if (c == 0) nx.g[dst] = sc;
 }
@@ -1596,7 +1604,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     int mean, const float* __restrict__ g, const int8_t* __restrict__ C8, int64_t ldc8,
     const _Float16* __restrict__ C16, int64_t ldc16, int par, int32_t d,
     const float* __restrict__ alpha, const float* __restrict__ bias, int relu,
-    float* __restrict__ out, int64_t ldo, int32_t rpb, NextLayer nx, int nbn,
+    float* __restrict__ out, int64_t ldo, int32_t rpb, NextLayer nx,
     const uint64_t* __restrict__ Bn, int64_t ldbn, const float* __restrict__ alpha_s) {
   constexpr int S = 64 / G;
   extern __shared__ uint64_t s_bn[];  // NX == 1: word 0 of each next weight column
@@ -1626,7 +1634,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     // the first LDS store:
     // thread t < 64 fetches column t's alpha, bias and alpha_self (zero past
     // d, the byte ranges ending there), and with NX == 1 thread t < d' word
-    // 0 of next weight column t (d' <= 256 threads).
+    // 0 of next weight column t (d' <= 64).
     const int t = threadIdx.x;
     const uint32_t eo = t < 64 ? (uint32_t)t * 4u : kPastEnd;
     const uint32_t eb4 = (uint32_t)d * 4u;
@@ -1932,7 +1940,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const bool fin = on && !headp && !tailp;
     if (base + S < o_e) {
       if (fin)
-        finish_slot<G, CPL, NX>(r_lo + idx, re - rs, mean, sum, ep, c, out, ldo, nx, nbn, s_bn);
+        finish_slot<G, CPL, NX>(r_lo + idx, re - rs, mean, sum, ep, c, out, ldo, nx, s_bn);
     } else {
 #pragma unroll
       for (int k = 0; k < CPL; ++k) keep_lds[k] = sum[k];
@@ -1961,7 +1969,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     }
   }
   if (__builtin_amdgcn_ballot_w64(keep_fin) != 0 && keep_fin)
-    finish_slot<G, CPL, NX>(keep_row, keep_re - keep_rs, mean, keep, ep, c, out, ldo, nx, nbn, s_bn);
+    finish_slot<G, CPL, NX>(keep_row, keep_re - keep_rs, mean, keep, ep, c, out, ldo, nx, s_bn);
 }
 
 // Rows cut by chunk boundaries: tail of the owning worker, then the heads of
@@ -2403,6 +2411,9 @@ hipError_t launch_bgemm_q8(const uint64_t* F, int64_t M, int64_t ldf,
                            int8_t* C8, int64_t ldc8, void* C16, int64_t ldc16,
                            float* g, hipStream_t stream) {
   if (M == 0) return hipSuccess;
+  // (its last tile's offsets reach up to 32 rows past the matrix)
+  if (bgemm_q8_e2m1_supported(M, N, K) && (uint64_t)(M + 32) * ldc8 <= 0xFFFFFFFFull)
+    return launch_bgemm_q8_e2m1(F, M, ldf, B, N, ldb, K, C8, ldc8, C16, ldc16, g, stream);
   constexpr int RM = 4;
   const int nb = q8_lane_bytes(N);
   const int kw = (K + 63) >> 6;
@@ -2494,14 +2505,13 @@ hipError_t spmm_q8_nb(int64_t n, int64_t nnz, const int64_t* rowptr,
                                  K, d, alpha, bias, relu, out, ldo, p, ws, fn, stream)
   if (fn.kind == 0) BIGCN_Q8S(0, 1);
   if (fn.kind == 2) BIGCN_Q8S(2, 1);
+  if (fn.kind == 4) BIGCN_Q8S(4, 1);
   if constexpr (NB >= 2) {
     if (fn.kind == 3) BIGCN_Q8S(3, 16 / NB);  // NBN: the self weights' words per lane
   }
-  switch (q8_lane_bytes(fn.d_out)) {
-    case 1: BIGCN_Q8S(1, 1);
-    case 2: BIGCN_Q8S(1, 2);
-    default: BIGCN_Q8S(1, 4);
-  }
+  // next products are formed in the epilogue for up to 64 columns
+  if (q8_lane_bytes(fn.d_out) != 1) return hipErrorInvalidValue;
+  BIGCN_Q8S(1, 1);
 #undef BIGCN_Q8S
 }
 
@@ -2522,17 +2532,18 @@ hipError_t spmm_narrow_gc(int64_t n, const int64_t* rowptr, const int32_t* colid
   const NextLayer nx = finish_args(mean, g, d, alpha, bias, relu, out, ldo, fn).nx;
   const int32_t rpb = narrow_rows_per_block(n);
   const dim3 grid((unsigned)((n + rpb - 1) / rpb));
-  const int nbn = fn.kind == 1 ? q8_lane_bytes(fn.d_out) : 1;
-  // one thread per next weight column stages its first word
-  if (fn.kind == 1 && fn.d_out > kBlock) return hipErrorInvalidValue;
+  // next products are formed in the epilogue for up to 64 columns
+  if (fn.kind == 1 && q8_lane_bytes(fn.d_out) != 1) return hipErrorInvalidValue;
+  if (fn.kind == 4 && fn.ldFn != 2) return hipErrorInvalidValue;
   const size_t lds = fn.kind == 1 ? (size_t)fn.d_out * sizeof(uint64_t) : 0;
 #define BIGCN_NARROW(NX)                                                                   \
   hipLaunchKernelGGL((k_spmm_narrow<G, CPL, NX>), grid, dim3(kBlock), lds, stream, n,      \
                      rowptr, colidx, mean, g, C8, ldc8, (const _Float16*)C16, ldc16, K & 1, \
-                     d, alpha, bias, relu, out, ldo, rpb, nx, nbn, fn.wbits, fn.ldw, fn.alpha_self)
+                     d, alpha, bias, relu, out, ldo, rpb, nx, fn.wbits, fn.ldw, fn.alpha_self)
   switch (fn.kind) {
     case 1: BIGCN_NARROW(1); break;
     case 2: BIGCN_NARROW(2); break;
+    case 4: BIGCN_NARROW(4); break;
     default: BIGCN_NARROW(0); break;
   }
 #undef BIGCN_NARROW

@@ -922,3 +922,15 @@ def test_fused_pack_gemm_matches_chained(dev, dims):
         bg.bigcn_bgemm_q8(F, wb, dims[0], C8, C16, gs)
         torch.cuda.synchronize()
         assert bool((gs[[3, 500, 1199]] < 0).all())
+
+
+# ------------------------------------ sign products on the matrix cores
+
+# Row tiles of 32 with remainders, 32-column tiles with remainders, the last
+# 64 inputs partly filled, and the most inputs the matrix-core GEMM takes
+# (640 for 129-256 columns, 1280 for 65-128) with one more.
+@pytest.mark.parametrize("M,N,K", [(1, 256, 64), (31, 65, 1), (32, 128, 63), (33, 129, 65),
+                                   (63, 96, 256), (64, 97, 257), (95, 256, 640), (40, 255, 641),
+                                   (41, 128, 1280), (42, 127, 1281), (2000, 160, 320)])
+def test_bgemm_q8_tile_edges(dev, M, N, K):
+    test_bgemm_q8_matches_oracle(dev, M, N, K)
