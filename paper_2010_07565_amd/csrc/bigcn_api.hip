@@ -111,19 +111,36 @@ struct ForwardLayout {
   int32_t dmax;
 };
 
-// Whether layer l's aggregation produces layer l+1's input in its epilogue
-// (see bigcn::FusedNext): both layers on the 8-bit path; packed signs (kind 4)
-// if layer l+1's products come from the matrix-core GEMM (wide layers: forming 65-256 products of a row by bit
-// counts in the epilogue takes longer than the GEMM, which is bound by
-// writing them), else its products (kind 1).
-int fuse_kind(int64_t n, int64_t nnz, const bigcn_layer* layers, int32_t nl, int32_t l) {
-  if (l + 1 >= nl || nnz == 0) return 0;
+// Whether layer l's aggregation forms layer l+1's input in its epilogue: both
+// on the 8-bit path.
+bool fuses_next(int64_t n, int64_t nnz, const bigcn_layer* layers, int32_t nl, int32_t l) {
+  if (l + 1 >= nl || nnz == 0) return false;
   const bigcn_layer& a = layers[l];
   const bigcn_layer& b = layers[l + 1];
-  if (a.wbits_self != nullptr || b.wbits_self != nullptr) return 0;  // GraphSAGE layers
-  if (!bigcn::q8_supported(n, a.d_out, a.d_in)) return 0;  // producer: 8-bit wave kernel
-  if (!bigcn::q8_supported(n, b.d_out, b.d_in)) return 0;
-  return bigcn::bgemm_q8_e2m1_supported(n, b.d_out, b.d_in) ? 4 : 1;
+  if (a.wbits_self != nullptr || b.wbits_self != nullptr) return false;  // GraphSAGE layers
+  return bigcn::q8_supported(n, a.d_out, a.d_in) && bigcn::q8_supported(n, b.d_out, b.d_in);
+}
+
+// Whether layer l's aggregation gathers packed signs and forms the products
+// itself (launch_spmm_sign) instead of gathering ready 8-bit codes.
+bool sign_layer(int64_t n, int64_t nnz, const bigcn_layer* layers, int32_t nl, int32_t l) {
+  const bigcn_layer& ly = layers[l];
+  return bigcn::sign_supported(n, nnz, ly.d_out, ly.d_in, ly.wbits_self != nullptr,
+                               fuses_next(n, nnz, layers, nl, l));
+}
+
+// What layer l's aggregation leaves of layer l+1's input (the kinds of
+// bigcn::FusedNext): packed signs (4) if layer l+1's aggregation gathers those
+// or its products come from the matrix-core GEMM (wide layers: forming 65-256
+// products of a row by bit counts in the epilogue takes longer than the GEMM,
+// which is bound by writing them), else its products (1); 0: nothing.
+int fuse_kind(int64_t n, int64_t nnz, const bigcn_layer* layers, int32_t nl, int32_t l) {
+  if (!fuses_next(n, nnz, layers, nl, l)) return 0;
+  const bigcn_layer& b = layers[l + 1];
+  return sign_layer(n, nnz, layers, nl, l + 1) ||
+                 bigcn::bgemm_q8_e2m1_supported(n, b.d_out, b.d_in)
+             ? 4
+             : 1;
 }
 
 // Row stride (bytes of codes, or halves of exact products) of the 8-bit
@@ -553,10 +570,21 @@ bigcn_status bigcn_forward(int64_t n, int64_t nnz, const int64_t* rowptr,
     int8_t* C8 = (int8_t*)(ws + L.off_C8[set]);
     void* C16 = ws + L.off_C16[set];
     const bool q8 = bigcn::q8_supported(n, ly.d_out, ly.d_in);
+    const bool sign = sign_layer(n, nnz, layers, n_layers, l);
+    // a layer that gathers signs keeps them in its products' place
+    uint64_t* signs = sign ? (uint64_t*)C8 : F;
+    const int64_t ld_signs = bigcn::sign_row_words(ly.d_in);
     const IType ct = forward_itype(ly.d_in);
-    if (have_signs) {
-      e = bigcn::launch_bgemm_q8(F, n, bigcn::sign_row_words(ly.d_in), ly.wbits, ly.d_out, ly.ldw,
-                                 ly.d_in, C8, q8_row(ly.d_out), C16, q8_row(ly.d_out), g, s);
+    if (have_signs) {  // (row stride ld_signs)
+      if (!sign) {
+        e = bigcn::launch_bgemm_q8(signs, n, ld_signs, ly.wbits, ly.d_out, ly.ldw, ly.d_in, C8,
+                                   q8_row(ly.d_out), C16, q8_row(ly.d_out), g, s);
+        if (e != hipSuccess) return BIGCN_EHIP;
+      }
+    } else if (!have_products && sign) {
+      e = bigcn::launch_pack(hin, n, ly.d_in, ldin, l == 0 ? mu : nullptr,
+                             l == 0 ? rstd : nullptr, rowptr, norm == BIGCN_NORM_SYM, signs,
+                             ld_signs, g, s, slot);
       if (e != hipSuccess) return BIGCN_EHIP;
     } else if (!have_products && q8 && ly.wbits_self == nullptr &&
         bigcn::pack_bgemm_q8_supported(ly.d_in, ly.d_out, ldin)) {
@@ -603,8 +631,8 @@ bigcn_status bigcn_forward(int64_t n, int64_t nnz, const int64_t* rowptr,
         fn.alpha_self = ly.alpha_self;
         if (bigcn::self_in_epilogue_supported(nnz, ly.d_out, ly.d_in)) {
           fn.kind = 3;
-          fn.F = F;
-          fn.ldF = L.ldF;
+          fn.F = sign ? signs : F;
+          fn.ldF = sign ? ld_signs : L.ldF;
           fn.wself = ly.wbits_self;
           fn.ldw_self = ly.ldw_self;
           fn.kin = ly.d_in;
@@ -624,10 +652,15 @@ bigcn_status bigcn_forward(int64_t n, int64_t nnz, const int64_t* rowptr,
         fn.C16 = ws + L.off_C16[nset];
         fn.ldc16 = q8_row(nxt.d_out);
         fn.g = (float*)(ws + L.off_g[nset]);
-        fn.Fn = F;
+        fn.Fn = sign_layer(n, nnz, layers, n_layers, l + 1) ? (uint64_t*)fn.C8 : F;
         fn.ldFn = bigcn::sign_row_words(nxt.d_in);
       }
-      e = bigcn::launch_spmm_q8(n, nnz, rowptr, gcol, norm == BIGCN_NORM_MEAN, g, C8,
+      if (sign)
+        e = bigcn::launch_spmm_sign(n, nnz, rowptr, gcol, norm == BIGCN_NORM_MEAN, g, signs,
+                                    ly.wbits, ly.ldw, ly.d_in, ly.d_out, ly.alpha, ly.bias,
+                                    ly.act == BIGCN_ACT_RELU, hout, ldout, plan, wsp, &fn, s);
+      else
+        e = bigcn::launch_spmm_q8(n, nnz, rowptr, gcol, norm == BIGCN_NORM_MEAN, g, C8,
                                 q8_row(ly.d_out), C16, q8_row(ly.d_out), ly.d_in, ly.d_out,
                                 ly.alpha, ly.bias,
                                 ly.act == BIGCN_ACT_RELU, hout, ldout, plan, wsp, &fn, s);

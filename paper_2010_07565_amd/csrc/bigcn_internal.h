@@ -83,8 +83,8 @@ hipError_t launch_bgemm_q8_e2m1(const uint64_t* F, int64_t M, int64_t ldf, const
 //           aggregation's g and products use) and the self weights' packed
 //           W^T (wself [d][ldw_self], kin inputs) instead of read from Cself;
 //           see self_in_epilogue_supported.
-//   kind 4: the next layer's packed signs (Fn, rows of ldFn words) for
-//           launch_bgemm_q8.
+//   kind 4: the next layer's packed signs (Fn, rows of ldFn words) for an
+//           aggregation that forms its products itself (launch_spmm_sign).
 // g receives the next layer's per-node scale.
 struct FusedNext {
   int kind;
@@ -155,8 +155,20 @@ hipError_t launch_spmm_q8(int64_t n, int64_t nnz, const int64_t* rowptr,
                           const SpmmPlan& plan, void* workspace,
                           const FusedNext* next, hipStream_t stream);
 
-// Words of a packed sign row between fused layers (pad words zero).
+// Aggregation that gathers packed signs and forms the products itself on the
+// matrix cores: the sums, and every result, are those of launch_bgemm_q8 +
+// launch_spmm_q8 on the same signs and scales, bit for bit.  F: rows of
+// sign_row_words(K) words (pad bits and words zero), g: the unflagged scales,
+// wbits [d][ldw]: this layer's packed W^T.
+// fused: its epilogue forms the next layer's input (FusedNext kind 1 or 4).
+bool sign_supported(int64_t n, int64_t nnz, int32_t d, int32_t K, bool two_weight, bool fused);
 constexpr int64_t sign_row_words(int32_t K) { return K <= 128 ? 2 : 4; }
+hipError_t launch_spmm_sign(int64_t n, int64_t nnz, const int64_t* rowptr,
+                            const int32_t* colidx, int mean, const float* g,
+                            const uint64_t* F, const uint64_t* wbits, int64_t ldw, int32_t K,
+                            int32_t d, const float* alpha, const float* bias, int relu,
+                            float* out, int64_t ldo, const SpmmPlan& plan, void* workspace,
+                            const FusedNext* next, hipStream_t stream);
 
 // Source order of the forward pass (see bigcn_source_slots): slot[i] for
 // every node, colslot[e] = slot[colidx[e]]; workspace of SlotPlan::bytes.

@@ -934,3 +934,80 @@ def test_fused_pack_gemm_matches_chained(dev, dims):
                                    (41, 128, 1280), (42, 127, 1281), (2000, 160, 320)])
 def test_bgemm_q8_tile_edges(dev, M, N, K):
     test_bgemm_q8_matches_oracle(dev, M, N, K)
+
+
+_SIGN_GRAPHS = {}
+
+
+def _sign_graph(kind):
+    """Graphs large enough for the aggregations over packed signs: 2^21
+    entries ("small"), 2^23 ("large"), and "holes", small with rows that have
+    no entries before, between and after the others."""
+    if kind not in _SIGN_GRAPHS:
+        g = workloads.rmat_graph(*((60_000, 4_250_000, 5) if kind == "large"
+                                   else (40_001, 1_070_000, 6)))
+        if kind == "holes":
+            n = 3 * g.n + 500
+            deg = np.zeros(n, dtype=np.int64)
+            deg[250:250 + 3 * g.n:3] = np.diff(g.rowptr)
+            rowptr = np.concatenate([[0], np.cumsum(deg)])
+            g = workloads.Graph(n, rowptr, (3 * g.colidx.astype(np.int64) + 250).astype(np.int32))
+        _SIGN_GRAPHS[kind] = g
+    return _SIGN_GRAPHS[kind]
+
+
+@pytest.mark.parametrize("kind,norm,act,dims", [
+    ("small", "sym", "none", [1, 65]), ("small", "mean", "relu", [63, 128, 40]),
+    ("small", "sym", "none", [64, 256, 256, 7]), ("small", "mean", "none", [127, 129, 200, 3]),
+    ("small", "sym", "relu", [128, 193]), ("holes", "mean", "none", [100, 256, 47]),
+    ("holes", "sym", "relu", [65, 127, 128, 65]), ("large", "mean", "relu", [129, 65]),
+    ("large", "sym", "none", [256, 128, 128, 40]), ("large", "mean", "none", [255, 97, 5])])
+def test_forward_over_signs_equals_chained(dev, kind, norm, act, dims):
+    """Layers whose aggregation gathers packed signs, in both source orders
+    and with the hidden outputs asked for: bit for bit the chained entry
+    points, which gather ready products.  Two feature rows have the signs of
+    a weight column (the largest products)."""
+    g = _sign_graph(kind)
+    rng = np.random.default_rng(sum(dims))
+    L = len(dims) - 1
+    x = rng.standard_normal((g.n, dims[0])).astype(np.float32)
+    wts = [workloads.glorot_t(dims[i], dims[i + 1], rng) for i in range(L)]
+    for r in (250, g.n // 2):
+        x[r] = wts[0][r % dims[1]] * rng.uniform(0.5, 2.0, dims[0]).astype(np.float32)
+    bs = [rng.uniform(-0.1, 0.1, dims[i + 1]).astype(np.float32) for i in range(L)]
+    acts = [act] * L
+    rowptr_t, colidx_t = _t(g.rowptr, dev), _t(g.colidx, dev)
+    xt = _t(x, dev)
+    h, hs = xt, []
+    for l in range(L):
+        h, *_ = gpu_layer(dev, g, norm, None, wts[l], bs[l], act=acts[l], rowptr_t=rowptr_t,
+                          colidx_t=colidx_t, ht=h)
+        hs.append(h)
+    for so in (False, True):
+        model = bg.BiGCN(rowptr_t, colidx_t, wts, bs, acts, norm=norm, device=dev,
+                         source_order=so)
+        assert torch.equal(model.forward(xt), h)
+        hidden = [torch.full((g.n, d), np.nan, device=dev) for d in dims[1:-1]]
+        assert torch.equal(model.forward(xt, hidden=hidden), h)
+        for a, b in zip(hidden, hs):
+            assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dims", [[100, 256, 47], [65, 65, 128], [200, 128, 9]])
+def test_sage_forward_over_signs_equals_chained(dev, dims):
+    g = workloads.without_self_loops(_sign_graph("large"))
+    rng = np.random.default_rng(sum(dims))
+    L = len(dims) - 1
+    xt = _t(rng.standard_normal((g.n, dims[0])).astype(np.float32), dev)
+    wn = [workloads.glorot_t(dims[i], dims[i + 1], rng) for i in range(L)]
+    ws = [workloads.glorot_t(dims[i], dims[i + 1], rng) for i in range(L)]
+    bs = [rng.uniform(-0.1, 0.1, dims[i + 1]).astype(np.float32) for i in range(L)]
+    rowptr_t, colidx_t = _t(g.rowptr, dev), _t(g.colidx, dev)
+    h = xt
+    for l in range(L):
+        h, *_ = gpu_sage_layer(dev, g, None, ws[l], wn[l], bs[l], rowptr_t=rowptr_t,
+                               colidx_t=colidx_t, ht=h)
+    for so in (False, True):
+        model = bg.BiGCN(rowptr_t, colidx_t, wn, bs, norm="mean", device=dev,
+                         weights_self_t=ws, source_order=so)
+        assert torch.equal(model.forward(xt), h)
