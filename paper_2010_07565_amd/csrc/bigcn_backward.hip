@@ -13,6 +13,9 @@
 //                                                 operand; 64-row runs added to
 //                                                 fp64 partial sums per chunk of
 //                                                 rows, summed in order)
+//           or, where dζ itself is not asked for and H~ is the cheaper one to
+//           gather (signs and a scale per edge instead of fp32 gradients):
+//           (Ã H~)^T G, fp32 products of the matrix core (see signs_first)
 //   dH~   = dζ W~^T,      W~ = B diag(α);  dH = dH~ 1[|dH~| < 1]   (Eq. (14);
 //                                                 bf16 MFMA, the same split)
 //   dW    = Eq. (15) with 1[|W| < 1] for the derivative of sign.
@@ -84,12 +87,13 @@ __global__ __launch_bounds__(kB) void k_bwd_prep(
   if (blockIdx.x == 0 && threadIdx.x < d) ones[threadIdx.x] = 1.f;
 }
 
-// Column sums of Gm over a chunk of R rows (block = chunk), fp64, rows in
-// node order (row i at slot[i] when given; eight loads in flight); then the
-// chunks in order.
+// Column sums of Gm (zero where out is given and not positive) over a chunk of
+// R rows (block = chunk), fp64, rows in node order (row i at slot[i] when
+// given; eight loads in flight); then the chunks in order.
 __global__ __launch_bounds__(kB) void k_bwd_colsum_part(
     int64_t n, int32_t d, const float* __restrict__ Gm, int64_t ldm, int64_t R,
-    double* __restrict__ part, const int32_t* __restrict__ slot) {
+    double* __restrict__ part, const int32_t* __restrict__ slot,
+    const float* __restrict__ out, int64_t ldo) {
   const int64_t c = blockIdx.x;
   const int64_t i0 = c * R, i1 = std::min<int64_t>(n, i0 + R);
   auto row = [&](int64_t i) -> int64_t { return slot != nullptr ? (int64_t)slot[i] : i; };
@@ -100,10 +104,18 @@ __global__ __launch_bounds__(kB) void k_bwd_colsum_part(
       float v[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) v[u] = Gm[row(i + u) * ldm + k];
+      if (out != nullptr) {
+        float o[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) o[u] = out[(i + u) * ldo + k];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = o[u] > 0.f ? v[u] : 0.f;
+      }
 #pragma unroll
       for (int u = 0; u < 8; ++u) acc += (double)v[u];
     }
-    for (; i < i1; ++i) acc += (double)Gm[row(i) * ldm + k];
+    for (; i < i1; ++i)
+      acc += out == nullptr || out[i * ldo + k] > 0.f ? (double)Gm[row(i) * ldm + k] : 0.0;
     part[c * d + k] = acc;
   }
 }
@@ -323,6 +335,118 @@ __global__ __launch_bounds__(kB) void k_bwd_wtilde_mfma(
   }
 }
 
+// Partial sums of dW~^T = G^T X over a chunk of R rows, X = Ã H~ in fp32:
+//   part[c][j][k] = sum_{i in chunk c} G_ij X_ik  (G zero where RELU and out <= 0).
+// One wave per (chunk c, 64 columns j, 32 columns k): fp32 MFMA 32x32x2, whose
+// operands are a lane's own element of rows 2 s and 2 s + 1, so loads are whole
+// 128-byte lines and nothing is staged; each run of 64 rows is summed in fp32
+// and added to fp64 accumulators, in row order.  The waves of a block take the
+// column tiles of one chunk (the same rows, from the CU's cache) and the blocks
+// of a chunk run on one XCD.
+template <bool RELU>
+__global__ __launch_bounds__(kB) __attribute__((amdgpu_waves_per_eu(2))) void k_bwd_wtilde_f32(
+    int64_t n, int32_t d_in, int32_t d_out, const float* __restrict__ X, int64_t ldx,
+    const float* __restrict__ G, int64_t ldg, const float* __restrict__ out, int64_t ldo,
+    int64_t R, int32_t jtiles, int32_t ktiles, int64_t tasks, double* __restrict__ part) {
+  typedef float float16_t __attribute__((ext_vector_type(16)));
+  constexpr int kSteps = 8;  // row pairs loaded together
+  const int lane = threadIdx.x & 63;
+  const int half = lane >> 5, m = lane & 31;
+  // consecutive blocks go to the 8 XCDs in turn; the grid is a multiple of 8
+  const int64_t b = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int64_t t = b * (kB / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (t >= tasks) return;  // no barrier in this kernel
+  const int kt = (int)(t % ktiles);
+  const int jt = (int)((t / ktiles) % jtiles);
+  const int64_t c = t / ((int64_t)ktiles * jtiles);
+  const int64_t i0 = c * R, i1 = std::min<int64_t>(n, i0 + R);
+  // Byte offsets from a run's first row: rows past the chunk and columns past
+  // the matrix lie outside the buffers and read as zero.
+  constexpr uint32_t kOut = 0x80000000u;
+  const int k = 32 * kt + m;
+  const uint32_t sx = (uint32_t)ldx * 4u, sg = (uint32_t)ldg * 4u, so = (uint32_t)ldo * 4u;
+  const uint32_t xo = k < d_in ? half * sx + 4u * k : kOut;
+  uint32_t go[2], oo[2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    const int j = 64 * jt + 32 * a + m;
+    go[a] = j < d_out ? half * sg + 4u * j : kOut;
+    oo[a] = j < d_out ? half * so + 4u * j : kOut;
+  }
+  auto rsrc = [](const float* p, int64_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), (short)0, (int)bytes,
+                                             0x00020000);
+  };
+  auto load = [](__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+  };
+  float16_t acc[2];
+  double acc64[2][16];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc64[a][r] = 0.0;
+  struct Rows {
+    float x[kSteps], g[2][kSteps], o[2][kSteps];
+  };
+  auto fetch = [&](int64_t r0) {  // rows r0 .. r0 + 2 kSteps - 1
+    Rows v;
+    const int64_t left = std::min<int64_t>(i1 - r0, 2 * kSteps);  // (0 past the chunk)
+    const int64_t base = left > 0 ? r0 : i0;
+    const __amdgpu_buffer_rsrc_t rx = rsrc(X + base * ldx, left > 0 ? left * sx : 0);
+    const __amdgpu_buffer_rsrc_t rg = rsrc(G + base * ldg, left > 0 ? left * sg : 0);
+    const __amdgpu_buffer_rsrc_t ro =
+        RELU ? rsrc(out + base * ldo, left > 0 ? left * so : 0) : rg;
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+      v.x[s] = load(rx, xo + 2u * s * sx);
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        v.g[a][s] = load(rg, go[a] + 2u * s * sg);
+        if (RELU) v.o[a][s] = load(ro, oo[a] + 2u * s * so);
+      }
+    }
+    return v;
+  };
+  Rows cur = fetch(i0);
+  for (int64_t r0 = i0; r0 < i1; r0 += kWtRun) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[a][r] = 0.f;
+#pragma unroll 2
+    for (int p = 0; p < kWtRun; p += 2 * kSteps) {
+      const Rows nxt = fetch(r0 + p + 2 * kSteps);
+      __builtin_amdgcn_sched_barrier(0);  // the next rows' loads before these rows' products
+#pragma unroll
+      for (int s = 0; s < kSteps; ++s)
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          const float g = RELU && !(cur.o[a][s] > 0.f) ? 0.f : cur.g[a][s];
+          acc[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(g, cur.x[s], acc[a], 0, 0, 0);
+        }
+      cur = nxt;
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc64[a][r] += (double)acc[a][r];
+  }
+  if (k >= d_in) return;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int j = 64 * jt + 32 * a + 8 * (r >> 2) + 4 * half + (r & 3);
+      if (j < d_out) part[((int64_t)c * d_out + j) * d_in + k] = acc64[a][r];
+    }
+}
+
+// d ones.
+__global__ __launch_bounds__(kB) void k_bwd_ones(int32_t d, float* __restrict__ ones) {
+  if ((int)threadIdx.x < d) ones[threadIdx.x] = 1.f;
+}
+
 // dW~^T[j][k] = sum over chunks in order; fp64 kept for Eq. (15), fp32 copy
 // to the caller (optional).
 __global__ __launch_bounds__(kB) void k_bwd_wtilde_final(
@@ -511,6 +635,11 @@ inline int pow2_at_least(int v, int cap) {
 struct BwdLayout {
   int64_t kw, ldm, R, chunks, Rdb, chunks_db;
   int ntw, kgw, jtw, nth, kgh;
+  // dW~ from Ã H~ (signs_first), in the place of Gm and dζ: packed signs, ones,
+  // Ã H~ (rows of ldx) and the aggregation's plan; x_bytes: their size, x_room:
+  // the place.
+  int64_t ldx;
+  size_t off_xf, off_x1, off_x, off_xspmm, x_bytes, x_room;
   size_t off_F, off_beta, off_s, off_ones, off_Gm, off_dz, off_pdb, off_pw, off_wtd,
       off_spmm, bytes;
 };
@@ -558,7 +687,33 @@ BwdLayout bwd_layout(int64_t n, int64_t nnz, int32_t d_in, int32_t d_out) {
   L.off_spmm = off;
   off += bigcn::spmm_plan(n, nnz, d_out).bytes;
   L.bytes = off;
+  L.ldx = (d_in + 31) / 32 * 32;
+  L.off_xf = L.off_Gm;
+  L.off_x1 = L.off_xf + up256((size_t)n * bigcn::sign_row_words(d_in) * 8);
+  L.off_x = L.off_x1 + up256((size_t)d_in * 4);
+  L.off_xspmm = L.off_x + up256((size_t)n * L.ldx * 4);
+  L.x_bytes = L.off_xspmm + bigcn::spmm_plan(n, nnz, d_in).bytes - L.off_Gm;
+  L.x_room = L.off_pdb - L.off_Gm;
   return L;
+}
+
+// Whether dW~ is formed as (Ã H~)^T G.  It reads 16 or 32 bytes of signs and a
+// scale per edge where dζ = Ã^T G reads d_out fp32 values; both sums are over
+// the same structurally symmetric pattern.  Its buffers take the place of the
+// staged G and dζ, which it does without (the workspace stays as it was).  Where
+// they fit, dζ against signs:
+//   100 -> 256: 60 K nodes, 2.3 M entries 291 -> 148 us; 169 K, 2.5 M 531 -> 279 us;
+//     233 K, 115 M 12.8 -> 1.27 ms; 2.45 M, 126 M 19.7 -> 3.84 ms
+//   256 -> 256: 169 K, 2.5 M 616 -> 425 us; 233 K, 115 M 13.0 -> 1.94 ms
+//   40 -> 64: 2.7 K, 13 K 53 -> 48 us; 2.45 M, 126 M 5.28 -> 2.25 ms
+//   40 -> 48: 169 K, 2.5 M 167 -> 130 us (narrower gradients were not measured)
+//   256 -> 256: 20 K nodes, 108 K entries 100 -> 102 us: level, hence the bound.
+bool signs_first(int64_t n, int64_t nnz, int32_t d_in, int32_t d_out, int64_t ldg, int64_t ldo,
+                 const BwdLayout& L) {
+  constexpr int64_t kMost = (1ll << 31) - 1;  // the kernels' buffer offsets have 31 bits
+  return nnz > 0 && d_in <= 256 && (d_in <= 128 || nnz >= 1 << 20) && d_out >= 48 &&
+         L.x_bytes <= L.x_room && n * bigcn::sign_row_words(d_in) * 8 <= kMost &&
+         16 * 4 * ldg <= kMost && 16 * 4 * ldo <= kMost;
 }
 
 inline bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
@@ -691,6 +846,43 @@ bigcn_status bigcn_layer_backward(int64_t n, int64_t nnz, const int64_t* rowptr,
     if (e != hipSuccess) return BIGCN_EHIP; \
   } while (0)
 
+  const bool relu = act == BIGCN_ACT_RELU;
+  const bool x_path = dh == nullptr && dh_tilde == nullptr && dzeta == nullptr &&
+                      signs_first(n, nnz, d_in, d_out, ldg, relu ? ldo : 0, L);
+  if (x_path) {
+    uint64_t* xf = (uint64_t*)(ws + L.off_xf);
+    float* x1 = (float*)(ws + L.off_x1);
+    float* x = (float*)(ws + L.off_x);
+    if (db != nullptr)  // (db itself once G, out and h have been read: it may overlap them)
+      hipLaunchKernelGGL(k_bwd_colsum_part, dim3((unsigned)L.chunks_db), dim3(kB), 0, s, n,
+                         d_out, gout, ldg, L.Rdb, pdb, (const int32_t*)nullptr,
+                         relu ? out : nullptr, ldo);
+    // signs and β, with the source factor of Ã (in the source order if given)
+    BIGCN_CHECK(bigcn::launch_pack(h, n, d_in, ldh, nullptr, nullptr, rowptr, mean ? 0 : 1, xf,
+                                   bigcn::sign_row_words(d_in), beta, s, slot));
+    hipLaunchKernelGGL(k_bwd_ones, dim3(1), dim3(kB), 0, s, d_in, x1);
+    BIGCN_CHECK(bigcn::launch_spmm_scaled_signs(
+        n, nnz, rowptr, slot != nullptr ? colslot : colidx, mean, beta, xf, d_in, x1, x, L.ldx,
+        bigcn::spmm_plan(n, nnz, d_in), ws + L.off_xspmm, s));
+    const int32_t jt = (d_out + 63) / 64, kt = (d_in + 31) / 32;
+    const int64_t tasks = L.chunks * jt * kt;
+    const dim3 grid((unsigned)(((tasks + 3) / 4 + 7) / 8 * 8));
+    if (relu)
+      hipLaunchKernelGGL(k_bwd_wtilde_f32<true>, grid, dim3(kB), 0, s, n, d_in, d_out, x, L.ldx,
+                         gout, ldg, out, ldo, L.R, jt, kt, tasks, pw);
+    else
+      hipLaunchKernelGGL(k_bwd_wtilde_f32<false>, grid, dim3(kB), 0, s, n, d_in, d_out, x, L.ldx,
+                         gout, ldg, (const float*)nullptr, (int64_t)0, L.R, jt, kt, tasks, pw);
+    if (db != nullptr)
+      hipLaunchKernelGGL(k_bwd_colsum_final, dim3(grid_of(d_out)), dim3(kB), 0, s, d_out,
+                         L.chunks_db, pdb, db);
+    hipLaunchKernelGGL(k_bwd_wtilde_final, dim3(grid_of((int64_t)d_in * d_out)), dim3(kB), 0, s,
+                       d_in, d_out, L.chunks, pw, wtd, dwt_tilde, lddwt);
+    hipLaunchKernelGGL(k_bwd_weights, dim3((unsigned)d_out), dim3(kB), 0, s, d_in, wtd, wbits,
+                       ldw, alpha, wt, ldwt, dwt, lddw);
+    BIGCN_CHECK(hipGetLastError());
+    return BIGCN_OK;
+  }
   // Signs and β of the layer input (Eqs. (7)-(8); no normalisation factor).
   if (n > 0)
     BIGCN_CHECK(bigcn::launch_pack(h, n, d_in, ldh, nullptr, nullptr, nullptr, 0, F, L.kw,
@@ -699,7 +891,6 @@ bigcn_status bigcn_layer_backward(int64_t n, int64_t nnz, const int64_t* rowptr,
     int lpr_log2 = 0;
     while ((1 << lpr_log2) * 4 < L.ldm) ++lpr_log2;  // lanes per staged row
     const int64_t rows_per_block = (kB / 64) * (64 >> lpr_log2);
-    const bool relu = act == BIGCN_ACT_RELU;
     // (d a multiple of 4 as well: no load reaches past a row's d entries)
     const bool vec = d_out % 4 == 0 && ldg % 4 == 0 && aligned(gout, 16) &&
                      (!relu || (ldo % 4 == 0 && aligned(out, 16)));
@@ -712,7 +903,8 @@ bigcn_status bigcn_layer_backward(int64_t n, int64_t nnz, const int64_t* rowptr,
   BIGCN_CHECK(hipGetLastError());
   if (db != nullptr) {
     hipLaunchKernelGGL(k_bwd_colsum_part, dim3((unsigned)L.chunks_db), dim3(kB), 0, s, n,
-                       d_out, Gsrc, ldsrc, L.Rdb, pdb, slot);
+                       d_out, Gsrc, ldsrc, L.Rdb, pdb, slot, (const float*)nullptr,
+                       (int64_t)0);
     hipLaunchKernelGGL(k_bwd_colsum_final, dim3(grid_of(d_out)), dim3(kB), 0, s, d_out,
                        L.chunks_db, pdb, db);
     BIGCN_CHECK(hipGetLastError());

@@ -114,7 +114,12 @@ __device__ inline float lane_float(float v, int i) {  // i wave-uniform
 // The layer's weights are read from LDS at every product (in registers they
 // left two waves per SIMD: 3.3 instead of 2.96 ms), at three waves per SIMD
 // half of the LDS rate.
-template <int KS, int NT, int NX, int NBN, int P>
+//
+// ID: the products are the signs themselves (the weights are the identity,
+// K columns): out = rowfac sum_e g_j sign(h_j), as the backward pass needs it.
+// Tile t's columns are then one dword of the signs, so it takes one product
+// (whatever KS), and the two operands it needs stay in registers.
+template <int KS, int NT, int NX, int NBN, int P, bool ID = false>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_spmm_sign(
     FinishArgs fa, int64_t n, int64_t nnz, const int64_t* __restrict__ rowptr,
     const int32_t* __restrict__ colidx, const float* __restrict__ g,
@@ -124,7 +129,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
     int64_t ldbn) {
   constexpr int NB = NT / 2;  // finished columns per lane
   extern __shared__ uint64_t sBn[];
-  __shared__ __attribute__((aligned(16))) int4_t s_w[NT * KS * 64];  // this layer's weights
+  __shared__ __attribute__((aligned(16))) int4_t s_w[ID ? 1 : NT * KS * 64];  // this layer's weights
   __shared__ float s_epi[3][256];
   __shared__ __attribute__((aligned(16))) float4_t s_ab[2][64];  // alpha, bias of a lane's columns
   __shared__ __attribute__((aligned(16))) float s_gw[kWavesPerBlock][32];
@@ -148,9 +153,22 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
     for (int i = 0; i < 4; ++i) v[i] &= mk[i];
     return v;
   };
-  for (int t = wave; t < NT; t += kWavesPerBlock)
+  // ID: -1/2 (set bits expand to -1) at the lane's column, for tiles of either
+  // half of the signs
+  int4_t one[2] = {};
+  if constexpr (ID) {
+    static_assert(NX == 0 && P == 0 && NT <= 2 * KS, "a sign dword per tile");
 #pragma unroll
-    for (int k = 0; k < KS; ++k) s_w[(t * KS + k) * 64 + lane] = weights(t, k);
+    for (int i = 0; i < 4; ++i) {
+      const int v = (lane & 3) == i ? (int)(9u << (4 * ((lane & 31) >> 2))) : 0;
+      one[0][i] = half == 0 ? v : 0;
+      one[1][i] = half == 0 ? 0 : v;
+    }
+  } else {
+    for (int t = wave; t < NT; t += kWavesPerBlock)
+#pragma unroll
+      for (int k = 0; k < KS; ++k) s_w[(t * KS + k) * 64 + lane] = weights(t, k);
+  }
   if (threadIdx.x < 128) {  // (zero past d)
     const bool al = threadIdx.x < 64;
     const float* src = al ? fa.alpha : fa.bias;
@@ -451,6 +469,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
           }
         }
         auto products = [&](int t) -> float16_t {
+          if constexpr (ID) return mfma_e2m1(av[t % KS], one[t / KS], c0);
           float16_t d = c0;
 #pragma unroll
           for (int k = 0; k < KS; ++k) d = mfma_e2m1(av[k], s_w[(t * KS + k) * 64 + lane], d);
@@ -640,7 +659,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
   }
 }
 
-template <int KS, int NT, int NX, int NBN>
+template <int KS, int NT, int NX, int NBN, bool ID = false>
 hipError_t sign_launch(int64_t n, int64_t nnz, const int64_t* rowptr, const int32_t* colidx,
                        const float* g, const uint64_t* F, const uint64_t* wbits, int64_t ldw,
                        int32_t K, const FinishArgs& fa, const SpmmPlan& p, void* ws,
@@ -661,13 +680,17 @@ hipError_t sign_launch(int64_t n, int64_t nnz, const int64_t* rowptr, const int3
   const int64_t waves = (p.workers + run - 1) / run;
   const dim3 grid((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock));
 #define BIGCN_SIGN(PV)                                                                       \
-  hipLaunchKernelGGL((k_spmm_sign<KS, NT, NX, NBN, PV>), grid, dim3(kBlock), lds, stream, fa, \
+  hipLaunchKernelGGL((k_spmm_sign<KS, NT, NX, NBN, PV, ID>), grid, dim3(kBlock), lds, stream, fa, \
                      n, nnz, rowptr, colidx, g, F, wbits, ldw, K, (int32_t)p.chunk, run, p.workers, p.dpad, \
                      tail_row, head, tail, wB, ldB)
-  if (K & 1)
-    BIGCN_SIGN(1);
-  else
+  if constexpr (ID) {
     BIGCN_SIGN(0);
+  } else {
+    if (K & 1)
+      BIGCN_SIGN(1);
+    else
+      BIGCN_SIGN(0);
+  }
 #undef BIGCN_SIGN
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -781,6 +804,26 @@ hipError_t launch_spmm_sign(int64_t n, int64_t nnz, const int64_t* rowptr,
   if (d <= 128) BIGCN_KSNT(2, 4);
   BIGCN_KSNT(2, 8);
 #undef BIGCN_KSNT
+}
+
+hipError_t launch_spmm_scaled_signs(int64_t n, int64_t nnz, const int64_t* rowptr,
+                                    const int32_t* colidx, int mean, const float* g,
+                                    const uint64_t* F, int32_t K, const float* ones, float* out,
+                                    int64_t ldo, const SpmmPlan& p, void* ws,
+                                    hipStream_t stream) {
+  // (the kernel's buffers address the signs and scales by 31-bit offsets)
+  if (n < 1 || nnz < 1 || K < 1 || K > 256 || n * sign_row_words(K) * 8 >= (1ll << 31) ||
+      p.dpad < 64 * q8_lane_bytes(K))
+    return hipErrorInvalidValue;
+  const FusedNext none = {};
+  const FinishArgs fa = finish_args(mean, g, K, ones, nullptr, 0, out, ldo, none);
+#define BIGCN_ID(KS, NT)                                                                    \
+  return sign_launch<KS, NT, 0, 1, true>(n, nnz, rowptr, colidx, g, F, nullptr, 0, K, fa, p, \
+                                         ws, none, stream)
+  if (K <= 64) BIGCN_ID(2, 2);
+  if (K <= 128) BIGCN_ID(2, 4);
+  BIGCN_ID(4, 8);
+#undef BIGCN_ID
 }
 
 }  // namespace bigcn

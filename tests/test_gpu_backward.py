@@ -136,6 +136,57 @@ def test_layer_backward_in_source_order_is_bit_identical(dev, norm, act):
         assert np.array_equal(a[k], b[k]), k
 
 
+@pytest.mark.parametrize("d_in,d_out", [(1, 48), (32, 48), (63, 65), (65, 64), (100, 256),
+                                        (128, 128), (129, 130), (200, 256), (256, 256)])
+@pytest.mark.parametrize("norm,act,source_order", [("sym", "none", True), ("mean", "relu", False),
+                                                   ("sym", "relu", True), ("mean", "none", False)])
+def test_weight_gradient_alone_matches_oracle(dev, norm, act, source_order, d_in, d_out):
+    """Without dh, dh_tilde and dzeta the weight gradient comes from the aggregated
+    scaled signs (X = Ã H~, dW~ = X^T G): widths on either side of the tiles of
+    32 and 64 columns and of the sign rows, rows that are no multiple of a run,
+    strided G and out, rows without entries; db, written last, over G's own memory."""
+    rng = np.random.default_rng(d_in + 3 * d_out + (norm == "mean"))
+    g = _star(777, rng)
+    e = g.nnz - 5                                 # the isolated nodes lose their self-loops
+    g = workloads.Graph(g.n, np.minimum(g.rowptr, e), np.ascontiguousarray(g.colidx[:e]))
+    h = rng.standard_normal((g.n, d_in)).astype(np.float32)
+    wt = (rng.standard_normal((d_out, d_in)) * 0.8).astype(np.float32)
+    G = (rng.standard_normal((g.n, d_out)) * 0.1).astype(np.float32)
+    out = rng.standard_normal((g.n, d_out)).astype(np.float32) if act == "relu" else None
+    ref = oracle.layer_backward(g.rowptr, g.colidx, norm, h, wt, G, out=out, act=act)
+    rowptr, colidx, wt_t = _t(g.rowptr, dev), _t(g.colidx, dev), _t(wt, dev)
+    wbits, alpha = bg.pack_weights(wt_t)
+    slot = colslot = None
+    if source_order:
+        slot = torch.empty(g.n, dtype=torch.int32, device=dev)
+        colslot = torch.empty(g.nnz, dtype=torch.int32, device=dev)
+        sws = torch.empty(bg.source_slots_workspace_bytes(g.n), dtype=torch.uint8, device=dev)
+        bg.bigcn_source_slots(rowptr, colidx, slot, colslot, sws)
+    Gt = torch.full((g.n, d_out + 3), np.nan, device=dev)
+    Gt[:, 1:1 + d_out] = _t(G, dev)
+    ot = None
+    if out is not None:
+        ot = torch.full((g.n, d_out + 1), np.nan, device=dev)
+        ot[:, :d_out] = _t(out, dev)
+        ot = ot[:, :d_out]
+    ws = torch.full((bg.layer_backward_workspace_bytes(g.n, g.nnz, d_in, d_out),), 255,
+                    dtype=torch.uint8, device=dev)
+    dwt = torch.full((d_out, d_in), np.nan, device=dev)
+    dwt_tilde = torch.full((d_out, d_in), np.nan, device=dev)
+    db = Gt[0, 1:1 + d_out]                       # the first row of G
+    bg.bigcn_layer_backward(rowptr, colidx, _t(h, dev), wt_t, wbits, alpha, Gt[:, 1:1 + d_out],
+                            dwt, ws, norm, act, out=ot, dwt_tilde=dwt_tilde, db=db, slot=slot,
+                            colslot=colslot)
+    torch.cuda.synchronize()
+    Gm = np.where(out > 0, G, 0) if act == "relu" else G
+    f64 = lambda t: t.cpu().numpy().astype(np.float64)  # noqa: E731
+    assert _err(f64(dwt_tilde), ref["dwt_tilde"], ref["mass_dwt"]) <= TOL
+    assert _err(f64(db), ref["db"], np.abs(Gm.astype(np.float64)).sum(axis=0)) <= TOL
+    a64 = np.abs(wt.astype(np.float64)).mean(axis=1)
+    mass_w = ref["mass_dwt"].sum(axis=1, keepdims=True) / d_in + a64[:, None] * ref["mass_dwt"]
+    assert _err(f64(dwt), ref["dwt"], mass_w) <= TOL
+
+
 def test_layer_backward_without_edges(dev):
     rng = np.random.default_rng(9)
     n, d_in, d_out = 50, 70, 5
