@@ -284,7 +284,7 @@ bigcn_status bigcn_spmm_csr_sage_q8(int64_t n, int64_t nnz, const int64_t* rowpt
  *   workspace  bigcn_layer_backward_workspace_bytes(n, nnz, d_in, d_out)
  *          bytes, 256-byte aligned; contents on entry are ignored.
  * Sums over nodes (db, dW~) are formed in fp64 over fixed chunks of rows
- * and added in order; every result is reproducible bit for bit.
+ * and added in a fixed order; every result is reproducible bit for bit.
  * Errors: EINVAL (bad sizes, NULL required pointers, short leading
  *         dimensions, bad norm / act, only one of slot / colslot), EALIGN
  *         (pointers not aligned to their element size, workspace not

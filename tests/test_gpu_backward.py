@@ -187,6 +187,24 @@ def test_weight_gradient_alone_matches_oracle(dev, norm, act, source_order, d_in
     assert _err(f64(dwt), ref["dwt"], mass_w) <= TOL
 
 
+@pytest.mark.parametrize("n,d_in,d_out", [(70001, 3, 2), (70001, 17, 33), (5000, 65, 7),
+                                          (257, 1, 1), (20011, 256, 3)])
+def test_gradient_sums_over_chunks(dev, n, d_in, d_out):
+    """db and dW~ over one to 1024 chunks of rows, cut into one to 64 runs: a
+    graph of self-loops only, where dζ = G."""
+    rng = np.random.default_rng(n + d_in)
+    g = workloads.Graph(n, np.arange(n + 1, dtype=np.int64), np.arange(n, dtype=np.int32))
+    h = rng.standard_normal((n, d_in)).astype(np.float32)
+    wt = (rng.standard_normal((d_out, d_in)) * 0.8).astype(np.float32)
+    G = (rng.standard_normal((n, d_out)) * 0.1).astype(np.float32)
+    got = gpu_backward(dev, g, "mean", h, wt, G)
+    G64 = G.astype(np.float64)
+    assert _err(got["db"], G64.sum(axis=0), np.abs(G64).sum(axis=0)) <= TOL
+    beta = np.abs(h.astype(np.float64)).mean(axis=1)[:, None]
+    dwt_tilde = G64.T @ (np.where(h >= 0, 1.0, -1.0) * beta)
+    assert _err(got["dwt_tilde"], dwt_tilde, np.abs(G64).T @ (beta + 0 * h)) <= TOL
+
+
 def test_layer_backward_without_edges(dev):
     rng = np.random.default_rng(9)
     n, d_in, d_out = 50, 70, 5
