@@ -151,6 +151,15 @@ __device__ inline void stage_weights(uint64_t* sB, const uint64_t* __restrict__ 
   __syncthreads();
 }
 
+// a + b where b may be a product: b is rounded first (no fused multiply-add),
+// so that the self term of a two-weight layer is the same whichever kernel adds
+// it.  (A select between the product and the sum did not keep the compiler from
+// contracting them in every kernel.)
+__device__ inline float add_rounded(float a, float b) {
+#pragma clang fp contract(off)
+  return a + b;
+}
+
 __device__ inline float act(float v, int relu) { return relu ? fmaxf(v, 0.f) : v; }
 
 // Destination-side factor of Ã for a row with deg entries: D̂^-1/2 (mean 0,
@@ -399,8 +408,6 @@ __device__ inline void finish_row(int64_t r, int64_t deg, const float4_t acc,
     for (int c = 0; c < NB; ++c)
       cs[c] = (float)__builtin_bit_cast(
           _Float16, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsc, (lane + 64 * c) * 2, 0, 0));
-    // (a select, not a product with zero: the product must round before it is
-    // added, as where the self term is formed from signs)
 #pragma unroll
     for (int c = 0; c < NB; ++c)
       self[c] = valid[c] ? gi * (EPI_LDS ? s_epi[2][lane + 64 * c] : er.alpha_s[c]) * cs[c] : 0.f;
@@ -411,7 +418,7 @@ __device__ inline void finish_row(int64_t r, int64_t deg, const float4_t acc,
     const float al = EPI_LDS ? s_epi[0][lane + 64 * c] : er.alpha[c];
     const float bi = EPI_LDS ? s_epi[1][lane + 64 * c] : er.bias[c];
     float t = deg > 0 ? fmaf(acc[c], rowfac * al, bi) : bi;
-    if (NX == 2 || NX == 3) t += self[c];
+    if (NX == 2 || NX == 3) t = add_rounded(t, self[c]);
     v[c] = act(t, fa.relu);
   }
   // Loads and stores go through buffers that end with the row, so lanes past

@@ -276,7 +276,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
 #pragma unroll
     for (int c = 0; c < NB; ++c) {
       float t = fmaf(acc[c], rf * al[c], bi[c]);
-      if (NX == 3) t += self[c];
+      if (NX == 3) t = add_rounded(t, self[c]);
       v[c] = act(t, f.relu);
     }
     if ((NX != 1 && NX != 4) || f.out != nullptr) {  // (see finish_row)
