@@ -259,6 +259,8 @@ bigcn_status bigcn_spmm_csr_sage_q8(int64_t n, int64_t nnz, const int64_t* rowpt
  *   G     = gout, masked by 1[out > 0] when act is RELU
  *   db    = sum_i G_i                       dζ = Ã^T G
  *   dW~   = H~^T dζ,   H~ = diag(β) sign(H) (Eqs. (7)-(8))
+ *           (formed as (Ã H~)^T G where dh, dh_tilde and dzeta are NULL and
+ *            that reads less: the same sum in another order)
  *   dH~   = dζ W~^T,   W~ = sign(W) diag(α) (Eqs. (3)-(4))
  *   dH    = dH~ * 1[|dH~| < 1]              (Eq. (14), the indicator taken
  *                                            on |dH~| as printed)

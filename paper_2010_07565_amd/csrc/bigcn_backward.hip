@@ -635,6 +635,40 @@ inline int pow2_at_least(int v, int cap) {
   return p;
 }
 
+// Whether dW~ is formed as (Ã H~)^T G.  It reads 16 or 32 bytes of signs and a
+// scale per edge where dζ = Ã^T G reads d_out fp32 values; both sums are over
+// the same structurally symmetric pattern.  Its buffers take the place of the
+// staged G and dζ, which it does without.
+//
+// Per edge the signs cost the same for any d_out and grow with d_in (a pass per
+// 256 columns), as do writing and reading Ã H~; dζ grows with d_out.  Hence the
+// lines, dζ against signs (us; n nodes, entries):
+//   d_in <= 64: always.  50 -> 33: 2.7 K, 13 K 57 -> 48; 2.45 M, 126 M 4986 -> 2290
+//   65-128: 128 -> 64: 20 K, 108 K 64 -> 65 (level), 30 K, 0.83 M 94 -> 87, 169 K,
+//     2.5 M 220 -> 181; 128 -> 128: 20 K, 108 K 71 -> 66; 128 -> 256: 2.45 M, 126 M
+//     19700 -> 4000
+//   129-256: 256 -> 256: 20 K, 108 K 100 -> 102, 100 K, 0.9 M 332 -> 294, 233 K, 115 M
+//     13040 -> 1910; 256 -> 128: 100 K, 0.9 M 216 -> 234, 169 K, 2.5 M 356 -> 331;
+//     256 -> 64: 169 K, 2.5 M 269 -> 289, 30 K, 5.8 M 192 -> 159; 256 -> 33: 400 K,
+//     8.4 M (21 a row) 594 -> 587, 2.45 M, 126 M (52 a row) 5633 -> 4234
+//   wider, long rows: 300 -> 128: 30 K, 5.8 M 302 -> 250, but 169 K, 2.5 M 395 -> 451;
+//     602 -> 128: 30 K, 5.8 M 328 -> 409, 233 K, 115 M 6081 -> 4755; 1000 -> 256: 233 K,
+//     115 M 13640 -> 7810, 1000 -> 128: 6294 -> 7027
+//   (d_out below 33 was not measured)
+bool signs_first(int64_t n, int64_t nnz, int32_t d_in, int32_t d_out) {
+  constexpr int64_t M = 1 << 20;
+  const int64_t passes = (d_in + 255) / 256;
+  if (n < 1 || nnz < 1 || d_out < 33 || d_in > 1024 || n * passes * 32 >= (1ll << 31))
+    return false;  // (the last: 31-bit buffer offsets into the signs)
+  if (d_in <= 64) return true;
+  if (d_in <= 128) return d_out > 64 || nnz >= M / 2;
+  if (passes == 1) {
+    if (d_out > 128) return nnz >= M / 2;
+    return d_out > 64 ? nnz >= 2 * M : nnz >= 4 * M && nnz >= 32 * n;
+  }
+  return nnz >= 64 * n && d_out > 40 * passes && nnz >= (passes == 2 ? 4 * M : 16 * M);
+}
+
 // Workspace layout of bigcn_layer_backward, and the tiling of the two
 // matrix-core products: dW~ takes 16 x 16*ntw tiles (ntw <= 8), dH~
 // 32 x 16*nth tiles (nth <= 8: two row tiles share each ±1 operand), each
@@ -642,11 +676,12 @@ inline int pow2_at_least(int v, int cap) {
 struct BwdLayout {
   int64_t kw, ldm, R, chunks, Rdb, chunks_db;
   int ntw, kgw, jtw, nth, kgh;
-  // dW~ from Ã H~ (signs_first), in the place of Gm and dζ: packed signs, ones,
-  // Ã H~ (rows of ldx) and the aggregation's plan; x_bytes: their size, x_room:
-  // the place.
-  int64_t ldx;
-  size_t off_xf, off_x1, off_x, off_xspmm, x_bytes, x_room;
+  // dW~ from Ã H~ (signs_first), in the place of Gm and dζ (made large enough
+  // for it): packed signs (rows of ldxf words), ones, Ã H~ (rows of ldx) and the
+  // aggregation's plan (of width dx).
+  int64_t ldxf, ldx;
+  int32_t dx;
+  size_t off_xf, off_x1, off_x, off_xspmm;
   size_t off_F, off_beta, off_s, off_ones, off_Gm, off_dz, off_pdb, off_pw, off_wtd,
       off_spmm, bytes;
 };
@@ -685,6 +720,15 @@ BwdLayout bwd_layout(int64_t n, int64_t nnz, int32_t d_in, int32_t d_out) {
   off += up256((size_t)n * L.ldm * 4);
   L.off_dz = off;
   off += up256((size_t)n * L.ldm * 4);
+  L.dx = std::min(d_in, 256);
+  L.ldx = (d_in + 31) / 32 * 32;
+  L.ldxf = d_in <= 256 ? bigcn::sign_row_words(d_in) : (d_in + 255) / 256 * 4;
+  L.off_xf = L.off_Gm;
+  L.off_x1 = L.off_xf + up256((size_t)n * L.ldxf * 8);
+  L.off_x = L.off_x1 + up256((size_t)L.dx * 4);
+  L.off_xspmm = L.off_x + up256((size_t)n * L.ldx * 4);
+  if (signs_first(n, nnz, d_in, d_out))
+    off = std::max(off, up256(L.off_xspmm + bigcn::spmm_plan(n, nnz, L.dx).bytes));
   L.off_pdb = off;
   off += up256((size_t)L.chunks_db * d_out * 8);
   L.off_pw = off;
@@ -694,33 +738,7 @@ BwdLayout bwd_layout(int64_t n, int64_t nnz, int32_t d_in, int32_t d_out) {
   L.off_spmm = off;
   off += bigcn::spmm_plan(n, nnz, d_out).bytes;
   L.bytes = off;
-  L.ldx = (d_in + 31) / 32 * 32;
-  L.off_xf = L.off_Gm;
-  L.off_x1 = L.off_xf + up256((size_t)n * bigcn::sign_row_words(d_in) * 8);
-  L.off_x = L.off_x1 + up256((size_t)d_in * 4);
-  L.off_xspmm = L.off_x + up256((size_t)n * L.ldx * 4);
-  L.x_bytes = L.off_xspmm + bigcn::spmm_plan(n, nnz, d_in).bytes - L.off_Gm;
-  L.x_room = L.off_pdb - L.off_Gm;
   return L;
-}
-
-// Whether dW~ is formed as (Ã H~)^T G.  It reads 16 or 32 bytes of signs and a
-// scale per edge where dζ = Ã^T G reads d_out fp32 values; both sums are over
-// the same structurally symmetric pattern.  Its buffers take the place of the
-// staged G and dζ, which it does without (the workspace stays as it was).  Where
-// they fit, dζ against signs:
-//   100 -> 256: 60 K nodes, 2.3 M entries 291 -> 148 us; 169 K, 2.5 M 531 -> 279 us;
-//     233 K, 115 M 12.8 -> 1.27 ms; 2.45 M, 126 M 19.7 -> 3.84 ms
-//   256 -> 256: 169 K, 2.5 M 616 -> 425 us; 233 K, 115 M 13.0 -> 1.94 ms
-//   40 -> 64: 2.7 K, 13 K 53 -> 48 us; 2.45 M, 126 M 5.28 -> 2.25 ms
-//   40 -> 48: 169 K, 2.5 M 167 -> 130 us (narrower gradients were not measured)
-//   256 -> 256: 20 K nodes, 108 K entries 100 -> 102 us: level, hence the bound.
-bool signs_first(int64_t n, int64_t nnz, int32_t d_in, int32_t d_out, int64_t ldg, int64_t ldo,
-                 const BwdLayout& L) {
-  constexpr int64_t kMost = (1ll << 31) - 1;  // the kernels' buffer offsets have 31 bits
-  return nnz > 0 && d_in <= 256 && (d_in <= 128 || nnz >= 1 << 20) && d_out >= 48 &&
-         L.x_bytes <= L.x_room && n * bigcn::sign_row_words(d_in) * 8 <= kMost &&
-         16 * 4 * ldg <= kMost && 16 * 4 * ldo <= kMost;
 }
 
 inline bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
@@ -854,8 +872,10 @@ bigcn_status bigcn_layer_backward(int64_t n, int64_t nnz, const int64_t* rowptr,
   } while (0)
 
   const bool relu = act == BIGCN_ACT_RELU;
+  constexpr int64_t kRowMax = 1 << 24;  // 16 rows within k_bwd_wtilde_f32's buffer offsets
   const bool x_path = dh == nullptr && dh_tilde == nullptr && dzeta == nullptr &&
-                      signs_first(n, nnz, d_in, d_out, ldg, relu ? ldo : 0, L);
+                      signs_first(n, nnz, d_in, d_out) && ldg <= kRowMax &&
+                      (!relu || ldo <= kRowMax);
   if (x_path) {
     uint64_t* xf = (uint64_t*)(ws + L.off_xf);
     float* x1 = (float*)(ws + L.off_x1);
@@ -866,11 +886,13 @@ bigcn_status bigcn_layer_backward(int64_t n, int64_t nnz, const int64_t* rowptr,
                          relu ? out : nullptr, ldo);
     // signs and β, with the source factor of Ã (in the source order if given)
     BIGCN_CHECK(bigcn::launch_pack(h, n, d_in, ldh, nullptr, nullptr, rowptr, mean ? 0 : 1, xf,
-                                   bigcn::sign_row_words(d_in), beta, s, slot));
-    hipLaunchKernelGGL(k_bwd_ones, dim3(1), dim3(kB), 0, s, d_in, x1);
-    BIGCN_CHECK(bigcn::launch_spmm_scaled_signs(
-        n, nnz, rowptr, slot != nullptr ? colslot : colidx, mean, beta, xf, d_in, x1, x, L.ldx,
-        bigcn::spmm_plan(n, nnz, d_in), ws + L.off_xspmm, s));
+                                   L.ldxf, beta, s, slot));
+    hipLaunchKernelGGL(k_bwd_ones, dim3(1), dim3(kB), 0, s, L.dx, x1);
+    for (int32_t k = 0; k < d_in; k += 256)  // 256 columns at a time
+      BIGCN_CHECK(bigcn::launch_spmm_scaled_signs(
+          n, nnz, rowptr, slot != nullptr ? colslot : colidx, mean, beta, xf + k / 64, L.ldxf,
+          std::min(d_in - k, 256), x1, x + k, L.ldx, bigcn::spmm_plan(n, nnz, L.dx),
+          ws + L.off_xspmm, s));
     const int32_t jt = (d_out + 63) / 64, kt = (d_in + 31) / 32;
     const int64_t tasks = L.chunks * jt * kt;
     const dim3 grid((unsigned)(((tasks + 3) / 4 + 7) / 8 * 8));

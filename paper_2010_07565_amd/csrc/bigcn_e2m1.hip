@@ -118,7 +118,8 @@ __device__ inline float lane_float(float v, int i) {  // i wave-uniform
 // ID: the products are the signs themselves (the weights are the identity,
 // K columns): out = rowfac sum_e g_j sign(h_j), as the backward pass needs it.
 // Tile t's columns are then one dword of the signs, so it takes one product
-// (whatever KS), and the two operands it needs stay in registers.
+// (whatever KS), and the two operands it needs stay in registers.  The rows of
+// F are ldw words apart there (W is not used).
 template <int KS, int NT, int NX, int NBN, int P, bool ID = false>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_spmm_sign(
     FinishArgs fa, int64_t n, int64_t nnz, const int64_t* __restrict__ rowptr,
@@ -197,7 +198,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
 #pragma unroll
   for (int i = 0; i < 16; ++i) c0[i] = P != 0 ? -0.5f : 0.f;
 
-  const __amdgpu_buffer_rsrc_t rsf = raw_rsrc(F, (uint32_t)(n * (KS * 8)));
+  const __amdgpu_buffer_rsrc_t rsf = raw_rsrc(
+      F, ID ? (uint32_t)((n - 1) * ldw * 8 + KS * 8) : (uint32_t)(n * (KS * 8)));
+  const uint32_t f_row = ID ? (uint32_t)ldw * 8u : KS * 8u;
   const __amdgpu_buffer_rsrc_t rsg = raw_rsrc(g, (uint32_t)(n * 4));
   const __amdgpu_buffer_rsrc_t rsi = raw_rsrc(colidx + s, (uint32_t)len * 4u);
   // this lane's matrix row: block mb of the tile, edge me of the block
@@ -412,7 +415,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
       };
       auto gather = [&](const Next& x) -> Tile {
         Tile tl;
-        const uint32_t fo = (x.j * (KS * 8u) + half * (KS * 4u)) | x.bad;
+        const uint32_t fo = (x.j * f_row + half * (KS * 4u)) | x.bad;
         const uint32_t go = (x.j * 4u) | (half != 0 ? kPastEnd : 0u) | x.bad;
         if constexpr (KS == 4) {
           const uint4_v v = __builtin_bit_cast(
@@ -808,17 +811,17 @@ hipError_t launch_spmm_sign(int64_t n, int64_t nnz, const int64_t* rowptr,
 
 hipError_t launch_spmm_scaled_signs(int64_t n, int64_t nnz, const int64_t* rowptr,
                                     const int32_t* colidx, int mean, const float* g,
-                                    const uint64_t* F, int32_t K, const float* ones, float* out,
-                                    int64_t ldo, const SpmmPlan& p, void* ws,
-                                    hipStream_t stream) {
+                                    const uint64_t* F, int64_t ldf, int32_t K,
+                                    const float* ones, float* out, int64_t ldo,
+                                    const SpmmPlan& p, void* ws, hipStream_t stream) {
   // (the kernel's buffers address the signs and scales by 31-bit offsets)
-  if (n < 1 || nnz < 1 || K < 1 || K > 256 || n * sign_row_words(K) * 8 >= (1ll << 31) ||
-      p.dpad < 64 * q8_lane_bytes(K))
+  if (n < 1 || nnz < 1 || K < 1 || K > 256 || ldf < sign_row_words(K) ||
+      n * ldf * 8 >= (1ll << 31) || p.dpad < 64 * q8_lane_bytes(K))
     return hipErrorInvalidValue;
   const FusedNext none = {};
   const FinishArgs fa = finish_args(mean, g, K, ones, nullptr, 0, out, ldo, none);
 #define BIGCN_ID(KS, NT)                                                                    \
-  return sign_launch<KS, NT, 0, 1, true>(n, nnz, rowptr, colidx, g, F, nullptr, 0, K, fa, p, \
+  return sign_launch<KS, NT, 0, 1, true>(n, nnz, rowptr, colidx, g, F, nullptr, ldf, K, fa, p, \
                                          ws, none, stream)
   if (K <= 64) BIGCN_ID(2, 2);
   if (K <= 128) BIGCN_ID(2, 4);

@@ -171,13 +171,14 @@ hipError_t launch_spmm_sign(int64_t n, int64_t nnz, const int64_t* rowptr,
                             const FusedNext* next, hipStream_t stream);
 
 // out_i = rowfac_i sum_e g_j sign(h_j), the aggregation of K <= 256 scaled
-// signs (mean as for launch_spmm): F and g as for launch_spmm_sign, ones: K
-// ones, p: a plan of width K, n sign_row_words(K) 8 below 2 GiB.
+// signs (mean as for launch_spmm): g as for launch_spmm_sign, F: rows of at
+// least sign_row_words(K) words (signs past K in them are not used), 8 ldf
+// bytes apart and below 2 GiB in all, ones: K ones, p: a plan of width K.
 hipError_t launch_spmm_scaled_signs(int64_t n, int64_t nnz, const int64_t* rowptr,
                                     const int32_t* colidx, int mean, const float* g,
-                                    const uint64_t* F, int32_t K, const float* ones, float* out,
-                                    int64_t ldo, const SpmmPlan& p, void* ws,
-                                    hipStream_t stream);
+                                    const uint64_t* F, int64_t ldf, int32_t K,
+                                    const float* ones, float* out, int64_t ldo,
+                                    const SpmmPlan& p, void* ws, hipStream_t stream);
 
 // Source order of the forward pass (see bigcn_source_slots): slot[i] for
 // every node, colslot[e] = slot[colidx[e]]; workspace of SlotPlan::bytes.

@@ -149,6 +149,28 @@ def test_weight_gradient_alone_matches_oracle(dev, norm, act, source_order, d_in
     g = _star(777, rng)
     e = g.nnz - 5                                 # the isolated nodes lose their self-loops
     g = workloads.Graph(g.n, np.minimum(g.rowptr, e), np.ascontiguousarray(g.colidx[:e]))
+    _check_weight_gradient_alone(dev, rng, g, norm, act, source_order, d_in, d_out)
+
+
+@pytest.mark.parametrize("n,d_in,d_out,norm,act,source_order", [
+    (1100, 65, 64, "sym", "none", True), (1100, 128, 33, "mean", "relu", False),
+    (1100, 129, 130, "mean", "none", True), (1100, 256, 256, "sym", "relu", False),
+    (3000, 193, 48, "sym", "none", False), (3000, 200, 65, "mean", "relu", True),
+    (3000, 257, 96, "sym", "relu", True), (3000, 512, 129, "mean", "none", False),
+    (5200, 602, 129, "sym", "none", True), (5200, 1024, 161, "mean", "relu", False)])
+def test_weight_gradient_alone_of_long_rows(dev, n, d_in, d_out, norm, act, source_order):
+    """The same where the choice between the two orders asks for 0.5, 4 and 16 M
+    entries: wider inputs, and several passes of 256 columns over the graph."""
+    rng = np.random.default_rng(n + d_in + 3 * d_out)
+    adj = np.triu(rng.random((n, n)) < 0.65, 1)
+    adj = adj | adj.T | np.eye(n, dtype=bool)
+    rowptr = np.concatenate([[0], np.cumsum(adj.sum(axis=1))]).astype(np.int64)
+    g = workloads.Graph(n, rowptr, np.nonzero(adj)[1].astype(np.int32))
+    assert g.nnz >= {1100: 1 << 19, 3000: 1 << 22, 5200: 1 << 24}[n]
+    _check_weight_gradient_alone(dev, rng, g, norm, act, source_order, d_in, d_out)
+
+
+def _check_weight_gradient_alone(dev, rng, g, norm, act, source_order, d_in, d_out):
     h = rng.standard_normal((g.n, d_in)).astype(np.float32)
     wt = (rng.standard_normal((d_out, d_in)) * 0.8).astype(np.float32)
     G = (rng.standard_normal((g.n, d_out)) * 0.1).astype(np.float32)
