@@ -278,7 +278,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
     const float4_t al = s_ab[0][lane], bi = s_ab[1][lane];
 #pragma unroll
     for (int c = 0; c < NB; ++c) {
-      float t = fmaf(acc[c], rf * al[c], bi[c]);
+      // (rf is zero for a row without entries only: not 0 * alpha, which may overflow)
+      float t = rf > 0.f ? fmaf(acc[c], rf * al[c], bi[c]) : bi[c];
       if (NX == 3) t = add_rounded(t, self[c]);
       v[c] = act(t, f.relu);
     }
@@ -296,7 +297,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
 #pragma unroll
       for (int c = 0; c < NB; ++c) {
         word[c] = __builtin_amdgcn_ballot_w64(lane + 64 * c < f.d && v[c] >= 0.f);
-        l1 += fabsf(v[c]);
+        // (past d the sums are of zeros only while every scale is finite)
+        l1 += lane + 64 * c < f.d ? fabsf(v[c]) : 0.f;
       }
       l1 = wave_sum(l1);
       if constexpr (NX == 4) {

@@ -993,6 +993,43 @@ def test_forward_over_signs_equals_chained(dev, kind, norm, act, dims):
             assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("dims", [[2, 100, 47], [66, 200, 128, 7], [127, 100, 65], [100, 100]])
+def test_forward_over_signs_when_a_scale_overflows(dev, dims):
+    """Finite inputs whose scale overflows fp32, at widths that leave lanes of
+    the last 64 columns idle, equal the chained entry points: a node's features
+    (its neighbours' values are infinite, not NaN: its products are all +-K)
+    and, for a single layer, a weight column (rows without entries still give
+    the bias)."""
+    g = _sign_graph("holes")
+    rng = np.random.default_rng(sum(dims))
+    L, K = len(dims) - 1, dims[0]
+    x = rng.standard_normal((g.n, K)).astype(np.float32)
+    wts = [workloads.glorot_t(dims[i], dims[i + 1], rng) for i in range(L)]
+    if L == 1:
+        wts[0][3] = 3e38
+    else:
+        deg = np.diff(g.rowptr)
+        wts[0] = np.abs(wts[0])
+        if K % 2 == 0:
+            wts[0][::3] *= -1
+        x[np.flatnonzero(deg > 1)[np.argmin(deg[deg > 1])]] = 3e38
+    bs = [rng.uniform(-0.1, 0.1, dims[i + 1]).astype(np.float32) for i in range(L)]
+    rowptr_t, colidx_t = _t(g.rowptr, dev), _t(g.colidx, dev)
+    h, hs = _t(x, dev), []
+    for l in range(L):
+        h, *_ = gpu_layer(dev, g, "sym", None, wts[l], bs[l], rowptr_t=rowptr_t,
+                          colidx_t=colidx_t, ht=h)
+        hs.append(h)
+    assert any(bool(torch.isinf(v).any()) for v in hs)
+    for so in (False, True):
+        model = bg.BiGCN(rowptr_t, colidx_t, wts, bs, norm="sym", device=dev, source_order=so)
+        hidden = [torch.empty((g.n, d), device=dev) for d in dims[1:-1]]
+        for a, b in zip(hidden + [model.forward(_t(x, dev), hidden=hidden)], hs):
+            assert torch.equal(torch.isnan(a), torch.isnan(b))
+            assert torch.equal(a.nan_to_num(0.0, np.inf, -np.inf),
+                               b.nan_to_num(0.0, np.inf, -np.inf))
+
+
 @pytest.mark.parametrize("dims", [[100, 256, 47], [65, 65, 128], [200, 128, 9]])
 def test_sage_forward_over_signs_equals_chained(dev, dims):
     g = workloads.without_self_loops(_sign_graph("large"))
