@@ -362,13 +362,17 @@ __global__ __launch_bounds__(kB) void k_bwd_wtilde_mfma(
 //   part[c][j][k] = sum_{i in chunk c} G_ij X_ik  (G zero where RELU and out <= 0).
 // One wave per (chunk c, 64 columns j, 32 columns k): fp32 MFMA 32x32x2, whose
 // operands are a lane's own element of rows 2 s and 2 s + 1, so loads are whole
-// 128-byte lines and nothing is staged; each run of 64 rows is summed in fp32
-// and added to fp64 accumulators, in row order.  The waves of a block take the
-// column tiles of one chunk (the same rows, from the CU's cache) and the blocks
-// of a chunk run on one XCD.  Bound by the fp32 matrix rate with 32-column
-// padding and by its loads, two waves per SIMD: 2.45 M x 256 x 100 in 1.53 ms
-// (82 TFLOP/s; with Ã H~ in 1.86 ms it replaces a 17.7 ms gather and a 1.15 ms
-// product).
+// 128-byte lines and nothing is staged; 16 rows at a time are summed in fp32
+// and added to fp64 accumulators, in row order.  (Each MFMA rounds a sum of two
+// rows more, where k_bwd_wtilde_mfma's take 32: with 64 rows in fp32 dW~ was up
+// to 1.5 times as far from its 64-bit value as that kernel's on graphs of short
+// rows, 1.40e-7 and 1.83e-7 against 1.08e-7 and 1.22e-7 relative for 40 -> 64 on
+// 2.7 K nodes; with 16, 1.02e-7 and 1.05e-7, and 0.3-0.94 times over the sweep
+// of the rule below.)  The waves of a block take the column tiles of one chunk
+// (the same rows, from the CU's cache) and the blocks of a chunk run on one XCD.
+// Bound by the fp32 matrix rate with 32-column padding, the fp64 additions and
+// its loads, two waves per SIMD: a 100 -> 256 layer of 2.45 M nodes takes 4.06 ms
+// in all (3.85 with 64-row runs; 20.5 by way of dζ).
 template <bool RELU>
 __global__ __launch_bounds__(kB) __attribute__((amdgpu_waves_per_eu(2))) void k_bwd_wtilde_f32(
     int64_t n, int32_t d_in, int32_t d_out, const float* __restrict__ X, int64_t ldx,
@@ -376,6 +380,7 @@ __global__ __launch_bounds__(kB) __attribute__((amdgpu_waves_per_eu(2))) void k_
     int64_t R, int32_t jtiles, int32_t ktiles, int64_t tasks, double* __restrict__ part) {
   typedef float float16_t __attribute__((ext_vector_type(16)));
   constexpr int kSteps = 8;  // row pairs loaded together
+  constexpr int kRuns = 2;   // such runs per loop pass (no register copies between them)
   const int lane = threadIdx.x & 63;
   const int half = lane >> 5, m = lane & 31;
   // consecutive blocks go to the 8 XCDs in turn; the grid is a multiple of 8
@@ -435,15 +440,15 @@ __global__ __launch_bounds__(kB) __attribute__((amdgpu_waves_per_eu(2))) void k_
     return v;
   };
   Rows cur = fetch(i0);
-  for (int64_t r0 = i0; r0 < i1; r0 += kWtRun) {
+  for (int64_t r0 = i0; r0 < i1; r0 += 2 * kSteps * kRuns) {
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][r] = 0.f;
-#pragma unroll 2
-    for (int p = 0; p < kWtRun; p += 2 * kSteps) {
-      const Rows nxt = fetch(r0 + p + 2 * kSteps);
+    for (int q = 0; q < kRuns; ++q) {
+      const Rows nxt = fetch(r0 + 2 * kSteps * (q + 1));
       __builtin_amdgcn_sched_barrier(0);  // the next rows' loads before these rows' products
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[a][r] = 0.f;
 #pragma unroll
       for (int s = 0; s < kSteps; ++s)
 #pragma unroll
@@ -451,12 +456,12 @@ __global__ __launch_bounds__(kB) __attribute__((amdgpu_waves_per_eu(2))) void k_
           const float g = RELU && !(cur.o[a][s] > 0.f) ? 0.f : cur.g[a][s];
           acc[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(g, cur.x[s], acc[a], 0, 0, 0);
         }
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc64[a][r] += (double)acc[a][r];
       cur = nxt;
     }
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc64[a][r] += (double)acc[a][r];
   }
   if (k >= d_in) return;
 #pragma unroll

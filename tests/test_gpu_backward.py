@@ -209,6 +209,34 @@ def _check_weight_gradient_alone(dev, rng, g, norm, act, source_order, d_in, d_o
     assert _err(f64(dwt), ref["dwt"], mass_w) <= TOL
 
 
+@pytest.mark.parametrize("n,m,d_in,d_out,norm", [
+    (2708, 5278, 40, 64, "sym"), (2708, 5278, 64, 200, "mean"), (20011, 44000, 100, 256, "sym"),
+    (20011, 300000, 128, 100, "mean"), (9001, 9000, 33, 48, "mean")])
+def test_weight_gradient_alone_is_as_precise(dev, n, m, d_in, d_out, norm):
+    """dW~ from the aggregated signs against dW~ by way of dζ (asked for here):
+    two orders of one sum, the first no further from the 64-bit result.  Both
+    distances are norms over thousands of independent roundings, which tell
+    two such sums apart to a few per cent; 1.1 allows for that."""
+    g = workloads.rmat_graph(n, m, 5)
+    rng = np.random.default_rng(n + d_in)
+    h = rng.standard_normal((g.n, d_in)).astype(np.float32)
+    wt = (rng.standard_normal((d_out, d_in)) * 0.1).astype(np.float32)
+    G = (rng.standard_normal((g.n, d_out)) * 0.05).astype(np.float32)
+    ref = oracle.layer_backward(g.rowptr, g.colidx, norm, h, wt, G)["dwt_tilde"]
+    rowptr, colidx, wt_t, Gt = _t(g.rowptr, dev), _t(g.colidx, dev), _t(wt, dev), _t(G, dev)
+    wbits, alpha = bg.pack_weights(wt_t)
+    ws = torch.empty(bg.layer_backward_workspace_bytes(g.n, g.nnz, d_in, d_out),
+                     dtype=torch.uint8, device=dev)
+    err = []
+    for dzeta in (torch.empty((g.n, d_out), device=dev), None):
+        dwt, dwt_tilde = (torch.empty((d_out, d_in), device=dev) for _ in range(2))
+        bg.bigcn_layer_backward(rowptr, colidx, _t(h, dev), wt_t, wbits, alpha, Gt, dwt, ws, norm,
+                                dwt_tilde=dwt_tilde, dzeta=dzeta)
+        err.append(np.linalg.norm(dwt_tilde.cpu().numpy() - ref))
+    assert err[0] != err[1]                       # (two orders indeed)
+    assert err[1] <= 1.1 * err[0]
+
+
 @pytest.mark.parametrize("n,d_in,d_out", [(70001, 3, 2), (70001, 17, 33), (5000, 65, 7),
                                           (257, 1, 1), (20011, 256, 3)])
 def test_gradient_sums_over_chunks(dev, n, d_in, d_out):
