@@ -649,19 +649,25 @@ inline int pow2_at_least(int v, int cap) {
 // staged G and dζ, which it does without.
 //
 // Per edge the signs cost the same for any d_out and grow with d_in (a pass per
-// 256 columns), as do writing and reading Ã H~; dζ grows with d_out.  Hence the
-// lines, dζ against signs (us; n nodes, entries):
-//   d_in <= 64: always.  50 -> 33: 2.7 K, 13 K 57 -> 48; 2.45 M, 126 M 4986 -> 2290
-//   65-128: 128 -> 64: 20 K, 108 K 64 -> 65 (level), 30 K, 0.83 M 94 -> 87, 169 K,
-//     2.5 M 220 -> 181; 128 -> 128: 20 K, 108 K 71 -> 66; 128 -> 256: 2.45 M, 126 M
-//     19700 -> 4000
-//   129-256: 256 -> 256: 20 K, 108 K 100 -> 102, 100 K, 0.9 M 332 -> 294, 233 K, 115 M
-//     13040 -> 1910; 256 -> 128: 100 K, 0.9 M 216 -> 234, 169 K, 2.5 M 356 -> 331;
-//     256 -> 64: 169 K, 2.5 M 269 -> 289, 30 K, 5.8 M 192 -> 159; 256 -> 33: 400 K,
-//     8.4 M (21 a row) 594 -> 587, 2.45 M, 126 M (52 a row) 5633 -> 4234
-//   wider, long rows: 300 -> 128: 30 K, 5.8 M 302 -> 250, but 169 K, 2.5 M 395 -> 451;
-//     602 -> 128: 30 K, 5.8 M 328 -> 409, 233 K, 115 M 6081 -> 4755; 1000 -> 256: 233 K,
-//     115 M 13640 -> 7810, 1000 -> 128: 6294 -> 7027
+// 256 columns); writing and reading Ã H~ costs d_in per node and pays only where
+// a node has enough entries; dζ grows with d_out.  Hence the lines, dζ against
+// signs (us; n nodes, entries):
+//   d_in <= 64: always.  40 -> 48: 2.7 K, 13 K 54 -> 50; 64 -> 48: 500 K, 2.1 M 293 -> 263;
+//     64 -> 47: 2.45 M, 126 M 5310 -> 2320
+//   65-128: 128 -> 65: 20 K, 108 K 73 -> 68, 130 K, 0.55 M 171 -> 151; 128 -> 48: 130 K,
+//     0.55 M (4 a row) 113 -> 124, but 100 K, 0.9 M (9) 124 -> 124, 40 K, 0.56 M 86 -> 85;
+//     100 -> 256: 2.45 M, 126 M 20500 -> 4060
+//   129-256: 256 -> 200: 130 K, 0.55 M (4 a row) 294 -> 339, 40 K, 0.56 M (14) 162 -> 161;
+//     200 -> 200: 100 K, 0.9 M (9) 278 -> 292, but 200 -> 256 320 -> 293; 256 -> 256: 130 K,
+//     0.55 M 349 -> 338, 233 K, 115 M 13040 -> 1910; 256 -> 144: 100 K, 1.3 M (13) 241 -> 275,
+//     30 K, 0.83 M (28) 140 -> 139, 256 -> 170 304 -> 275 and 153 -> 139; 256 -> 65: 500 K, 2.1 M (4) 635 -> 773,
+//     169 K, 2.5 M (15) 343 -> 349, 1.2 M, 12 M (10) 1918 -> 1857; 256 -> 48: 130 K, 4.2 M
+//     (33 a row) 237 -> 256, 65 K, 4.3 M (66) 178 -> 172; 256 -> 64: 130 K, 4.2 M 283 -> 266
+//   wider, rows of 64 entries and more: 300 -> 90: 65 K, 4.5 M 323 -> 296; 400 -> 129: 65 K,
+//     4.5 M 354 -> 402, but 400 -> 170 442 -> 405, and 400 -> 90: 200 K, 17 M 1100 -> 979;
+//     602 -> 129: 200 K, 17 M 1383 -> 1539, 602 -> 170 1774 -> 1565, 602 -> 128: 233 K, 115 M
+//     6081 -> 4755; 1000 -> 200: 200 K, 17 M 2244 -> 2543, 1000 -> 256 2692 -> 2525; 233 K,
+//     115 M 13640 -> 7810, 1000 -> 128 there 6294 -> 7027
 //   (d_out below 33 was not measured)
 bool signs_first(int64_t n, int64_t nnz, int32_t d_in, int32_t d_out) {
   constexpr int64_t M = 1 << 20;
@@ -669,12 +675,16 @@ bool signs_first(int64_t n, int64_t nnz, int32_t d_in, int32_t d_out) {
   if (n < 1 || nnz < 1 || d_out < 33 || d_in > 1024 || n * passes * 32 >= (1ll << 31))
     return false;  // (the last: 31-bit buffer offsets into the signs)
   if (d_in <= 64) return true;
-  if (d_in <= 128) return d_out > 64 || nnz >= M / 2;
+  if (d_in <= 128) return d_out > 64 || (nnz >= M / 2 && nnz >= 8 * n);
   if (passes == 1) {
-    if (d_out > 128) return nnz >= M / 2;
-    return d_out > 64 ? nnz >= 2 * M : nnz >= 4 * M && nnz >= 32 * n;
+    if (d_out > 240) return nnz >= M / 2;
+    if (d_out > 128) return nnz >= M / 2 && nnz >= (d_out > 160 ? 12 : 24) * n;
+    if (d_out > 64) return nnz >= 2 * M && nnz >= 10 * n;
+    return nnz >= 4 * M && nnz >= (d_out > 56 ? 32 : 48) * n;
   }
-  return nnz >= 64 * n && d_out > 40 * passes && nnz >= (passes == 2 ? 4 * M : 16 * M);
+  if (nnz < 64 * n || d_out <= 40 * passes) return false;
+  if (passes == 2) return nnz >= (d_in <= 320 || d_out >= 160 ? 4 * M : 16 * M);
+  return nnz >= (d_out >= (passes == 3 ? 160 : 240) ? 16 * M : 64 * M);
 }
 
 // Workspace layout of bigcn_layer_backward, and the tiling of the two

@@ -144,12 +144,15 @@ def test_weight_gradient_alone_matches_oracle(dev, norm, act, source_order, d_in
     """Without dh, dh_tilde and dzeta the weight gradient comes from the aggregated
     scaled signs (X = Ã H~, dW~ = X^T G): widths on either side of the tiles of
     32 and 64 columns and of the sign rows, rows that are no multiple of a run,
-    strided G and out, rows without entries; db, written last, over G's own memory."""
+    strided G and out, rows without entries; db, written last, over G's own memory.
+    (Inputs wider than 64 with outputs of at most 64, and wider than 128, take dζ's
+    order on a graph this small.)"""
     rng = np.random.default_rng(d_in + 3 * d_out + (norm == "mean"))
     g = _star(777, rng)
     e = g.nnz - 5                                 # the isolated nodes lose their self-loops
     g = workloads.Graph(g.n, np.minimum(g.rowptr, e), np.ascontiguousarray(g.colidx[:e]))
-    _check_weight_gradient_alone(dev, rng, g, norm, act, source_order, d_in, d_out)
+    _check_weight_gradient_alone(dev, rng, g, norm, act, source_order, d_in, d_out,
+                                 signs=d_in <= 64 or (d_in <= 128 and d_out > 64))
 
 
 @pytest.mark.parametrize("n,d_in,d_out,norm,act,source_order", [
@@ -157,20 +160,38 @@ def test_weight_gradient_alone_matches_oracle(dev, norm, act, source_order, d_in
     (1100, 129, 130, "mean", "none", True), (1100, 256, 256, "sym", "relu", False),
     (3000, 193, 48, "sym", "none", False), (3000, 200, 65, "mean", "relu", True),
     (3000, 257, 96, "sym", "relu", True), (3000, 512, 129, "mean", "none", False),
-    (5200, 602, 129, "sym", "none", True), (5200, 1024, 161, "mean", "relu", False)])
+    (5200, 602, 129, "sym", "none", True), (5200, 1024, 161, "mean", "relu", False),
+    (3000, 512, 160, "mean", "none", False), (5200, 400, 81, "sym", "relu", True),
+    (5200, 602, 160, "sym", "none", True), (5200, 1024, 241, "mean", "relu", False)])
 def test_weight_gradient_alone_of_long_rows(dev, n, d_in, d_out, norm, act, source_order):
     """The same where the choice between the two orders asks for 0.5, 4 and 16 M
-    entries: wider inputs, and several passes of 256 columns over the graph."""
+    entries: wider inputs, and several passes of 256 columns over the graph (three of
+    the cases lie on the other side of its lines)."""
     rng = np.random.default_rng(n + d_in + 3 * d_out)
     adj = np.triu(rng.random((n, n)) < 0.65, 1)
     adj = adj | adj.T | np.eye(n, dtype=bool)
     rowptr = np.concatenate([[0], np.cumsum(adj.sum(axis=1))]).astype(np.int64)
     g = workloads.Graph(n, rowptr, np.nonzero(adj)[1].astype(np.int32))
     assert g.nnz >= {1100: 1 << 19, 3000: 1 << 22, 5200: 1 << 24}[n]
-    _check_weight_gradient_alone(dev, rng, g, norm, act, source_order, d_in, d_out)
+    _check_weight_gradient_alone(dev, rng, g, norm, act, source_order, d_in, d_out,
+                                 signs=(d_in, d_out) not in [(512, 129), (602, 129), (1024, 161)])
 
 
-def _check_weight_gradient_alone(dev, rng, g, norm, act, source_order, d_in, d_out):
+@pytest.mark.parametrize("n,m,d_in,d_out,signs", [
+    (50021, 250000, 100, 48, True), (80001, 250000, 128, 64, False),
+    (40003, 262144, 200, 200, True), (50021, 250000, 200, 200, False),
+    (131072, 983040, 256, 65, True), (262147, 1048576, 256, 65, False)])
+def test_weight_gradient_alone_by_entries_a_row(dev, n, m, d_in, d_out, signs):
+    """Either side of the lines that ask for entries per row: Ã H~ is written and
+    read per node, so graphs of few entries a row keep dζ's order."""
+    rng = np.random.default_rng(n + d_in)
+    g = workloads.rmat_graph(n, m, 4)
+    _check_weight_gradient_alone(dev, rng, g, "mean", "none", False, d_in, d_out, signs)
+
+
+def _check_weight_gradient_alone(dev, rng, g, norm, act, source_order, d_in, d_out, signs):
+    """signs: whether this call sums the signs' way; the order by way of dζ, which
+    a call that asks for dζ takes, rounds differently."""
     h = rng.standard_normal((g.n, d_in)).astype(np.float32)
     wt = (rng.standard_normal((d_out, d_in)) * 0.8).astype(np.float32)
     G = (rng.standard_normal((g.n, d_out)) * 0.1).astype(np.float32)
@@ -195,11 +216,18 @@ def _check_weight_gradient_alone(dev, rng, g, norm, act, source_order, d_in, d_o
                     dtype=torch.uint8, device=dev)
     dwt = torch.full((d_out, d_in), np.nan, device=dev)
     dwt_tilde = torch.full((d_out, d_in), np.nan, device=dev)
+    other = torch.empty_like(dwt_tilde)
+    bg.bigcn_layer_backward(rowptr, colidx, _t(h, dev), wt_t, wbits, alpha, Gt[:, 1:1 + d_out],
+                            dwt, ws, norm, act, out=ot, dwt_tilde=other, slot=slot,
+                            colslot=colslot, dzeta=torch.empty((g.n, d_out), device=dev))
+    dwt.fill_(np.nan)
+    ws.fill_(255)
     db = Gt[0, 1:1 + d_out]                       # the first row of G
     bg.bigcn_layer_backward(rowptr, colidx, _t(h, dev), wt_t, wbits, alpha, Gt[:, 1:1 + d_out],
                             dwt, ws, norm, act, out=ot, dwt_tilde=dwt_tilde, db=db, slot=slot,
                             colslot=colslot)
     torch.cuda.synchronize()
+    assert torch.equal(dwt_tilde, other) != signs
     Gm = np.where(out > 0, G, 0) if act == "relu" else G
     f64 = lambda t: t.cpu().numpy().astype(np.float64)  # noqa: E731
     assert _err(f64(dwt_tilde), ref["dwt_tilde"], ref["mass_dwt"]) <= TOL
