@@ -57,6 +57,16 @@ __device__ inline float wave_sum(float v) {
   return (a + b) + (c + d);
 }
 
+// Between a wave's LDS stores and its lanes' loads of each other's values (and
+// the other way round): a wave's LDS operations complete in order, so it takes
+// no instruction, but neither the compiler's moves nor lanes run apart may
+// cross it.
+__device__ inline void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 typedef float float2_t __attribute__((ext_vector_type(2)));
 
 // Lane swaps between two registers: swap32 exchanges lanes 32..63 of a with
@@ -349,7 +359,9 @@ __device__ inline void load_row_words(uint64_t (&fw)[NW], const uint64_t* __rest
 
 // Lane 0's v to *p, and lanes 0 .. n - 1's words to p[0 .. n), through
 // buffers of that size (no branch on the lane, see finish_row).
-__device__ inline void store_first(float* p, int lane, float v) {
+template <typename T>
+__device__ inline void store_first(T* p, int lane, T v) {
+  static_assert(sizeof(T) == 4, "one dword");
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), raw_rsrc(p, 4u),
                                         lane * 4, 0, 0);
 }

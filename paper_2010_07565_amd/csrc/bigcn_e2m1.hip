@@ -126,14 +126,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
     const int32_t* __restrict__ colidx, const float* __restrict__ g,
     const uint64_t* __restrict__ F, const uint64_t* __restrict__ W, int64_t ldw, int32_t K,
     int32_t chunk, int32_t run, int64_t workers, int32_t dpad, int32_t* __restrict__ tail_row,
-    float* __restrict__ head, float* __restrict__ tail, const uint64_t* __restrict__ Bn,
+    float* __restrict__ head, float* __restrict__ tails, const uint64_t* __restrict__ Bn,
     int64_t ldbn) {
   constexpr int NB = NT / 2;  // finished columns per lane
   extern __shared__ uint64_t sBn[];
   __shared__ __attribute__((aligned(16))) int4_t s_w[ID ? 1 : NT * KS * 64];  // this layer's weights
   __shared__ float s_epi[3][256];
   __shared__ __attribute__((aligned(16))) float4_t s_ab[2][64];  // alpha, bias of a lane's columns
-  __shared__ __attribute__((aligned(16))) float s_gw[kWavesPerBlock][32];
+  __shared__ __attribute__((aligned(16))) float s_gw[kWavesPerBlock][64];
   const int lane = threadIdx.x & 63;
   const int wave = wave_index_in_block();
   const int half = lane >> 5;
@@ -238,13 +238,20 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
       const NextLayer nx = fresh_finish().nx;
       float sc = l1_l / (float)fa.d;
       if (nx.sym) sc = sc * rf_l;  // D̂^-1/2: the symmetric destination factor
-      if ((done >> lane) & 1) {
-        uint64_t* f = nx.Fn + (int64_t)dst_l * nx.ldFn;
+      // (rows of NB words; lanes without a finished row store past the end,
+      // without a branch in the window loop: see finish_row)
+      const uint32_t off = ((done >> lane) & 1) != 0 ? 0u : kPastEnd;
+      const __amdgpu_buffer_rsrc_t rsn = raw_rsrc(nx.Fn, (uint32_t)(n * (NB * 8)));
 #pragma unroll
-        for (int c = 0; c < NB; ++c)
-          if (c < nx.ldFn) f[c] = ((uint64_t)(uint32_t)whi[c] << 32) | (uint32_t)wlo[c];
-        nx.g[dst_l] = sc;
+      for (int c = 0; c < NB; c += 2) {
+        const uint4_v two = {(uint32_t)wlo[c], (uint32_t)whi[c], (uint32_t)wlo[c + 1],
+                             (uint32_t)whi[c + 1]};
+        __builtin_amdgcn_raw_buffer_store_b128(
+            two, rsn, (int)(((uint32_t)dst_l * (NB * 8u) + 8u * c) | off), 0, 0);
       }
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sc),
+                                            raw_rsrc(nx.g, (uint32_t)(n * 4)),
+                                            (int)((uint32_t)dst_l * 4u | off), 0, 0);
     }
   };
   // The epilogue of finish_row for row i of the window: the same operations,
@@ -447,7 +454,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
         const Next xn = look_up();
         const Tile nn = gather(xx);
         xx = xn;
-        if (half == 0) gw[lane] = cur.g;
+        wave_lds_sync();
+        gw[lane] = cur.g;  // (lanes 32-63: zero, not read)
+        wave_lds_sync();
         int4_t av[KS];
 #pragma unroll
         for (int k = 0; k < KS; ++k) av[k] = sign_nibbles<2>(cur.f[k]);
@@ -540,9 +549,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
       end_l = rowptr[base + lane < n ? base + lane + 1 : n];
       open_window();
     }
-    if (open_row < 0) {
-      if (lane == 0) tail_row[w] = -1;
-    } else {
+    int tail = -1;  // the row that goes on from this chunk
+    if (open_row >= 0) {
       const bool before = __builtin_amdgcn_readlane(st, open_row) < cs;
       float4_t sum = zero4;
 #pragma unroll
@@ -550,9 +558,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
         sum[c] = 2.f * both_chains(acc[2 * c], acc[2 * c + 1]);
         if constexpr (P != 0) sum[c] += gsum;
       }
-      store_partial<NB>((before ? head : tail) + w * dpad + NB * lane, sum);
-      if (lane == 0) tail_row[w] = before ? -1 : (int32_t)(base + open_row);
+      store_partial<NB>((before ? head : tails) + w * dpad + NB * lane, sum);
+      if (!before) tail = (int)(base + open_row);
     }
+    store_first(tail_row + w, lane, tail);
   }
   close_window();
 }
@@ -799,6 +808,7 @@ hipError_t launch_spmm_sign(int64_t n, int64_t nnz, const int64_t* rowptr,
   // a fused next layer of products (kind 1) has at most 64 columns here
   if (!sign_supported(n, nnz, d, K, fn.kind == 3, fn.kind == 1 || fn.kind == 4) ||
       (fn.kind == 1 && q8_lane_bytes(fn.d_out) != 1) ||
+      (fn.kind == 4 && fn.ldFn != q8_lane_bytes(d)) ||
       (fn.kind == 3 && !self_in_epilogue_supported(nnz, d, fn.kin)))
     return hipErrorInvalidValue;
   const FinishArgs fa = finish_args(mean, g, d, alpha, bias, relu, out, ldo, fn);

@@ -1133,7 +1133,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
   float* gw = &s_gw[wave_index_in_block()][0];
   for (int eb = 0; eb < nE; eb += 64) {
     const uint64_t flagged = __builtin_amdgcn_ballot_w64(__builtin_bit_cast(int, gA) < 0);
+    wave_lds_sync();
     gw[lane] = gA;
+    wave_lds_sync();
     for (int m = 0; m < 64; m += U) {
       const int e0 = eb + m;
       if (e0 >= nE) break;

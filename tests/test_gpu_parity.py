@@ -960,7 +960,8 @@ def _sign_graph(kind):
     ("small", "sym", "none", [1, 65]), ("small", "mean", "relu", [63, 128, 40]),
     ("small", "sym", "none", [64, 256, 256, 7]), ("small", "mean", "none", [127, 129, 200, 3]),
     ("small", "sym", "relu", [128, 193]), ("holes", "mean", "none", [100, 256, 47]),
-    ("holes", "sym", "relu", [65, 127, 128, 65]), ("large", "mean", "relu", [129, 65]),
+    ("holes", "sym", "relu", [65, 127, 128, 65]), ("holes", "sym", "none", [100, 200, 256, 7]),
+    ("large", "mean", "relu", [129, 65]),
     ("large", "sym", "none", [256, 128, 128, 40]), ("large", "mean", "none", [255, 97, 5])])
 def test_forward_over_signs_equals_chained(dev, kind, norm, act, dims):
     """Layers whose aggregation gathers packed signs, in both source orders
