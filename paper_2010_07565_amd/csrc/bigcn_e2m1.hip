@@ -256,7 +256,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
   };
   // The epilogue of finish_row for row i of the window: the same operations,
   // with what every row needs formed per window.
-  auto finish = [&](int i, const float4_t acc) {
+  // (rows without entries, empty, get the bias: not 0 * alpha, which may overflow)
+  auto finish = [&](int i, const float4_t acc, bool empty) {
     const FinishArgs f = NX == 0 || NX == 4 ? fa : fresh_finish();
     const float rf = lane_float(rf_l, i);
     const int64_t r = base + i;
@@ -285,8 +286,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
     const float4_t al = s_ab[0][lane], bi = s_ab[1][lane];
 #pragma unroll
     for (int c = 0; c < NB; ++c) {
-      // (rf is zero for a row without entries only: not 0 * alpha, which may overflow)
-      float t = rf > 0.f ? fmaf(acc[c], rf * al[c], bi[c]) : bi[c];
+      float t = empty ? bi[c] : fmaf(acc[c], rf * al[c], bi[c]);
       if (NX == 3) t = add_rounded(t, self[c]);
       v[c] = act(t, f.relu);
     }
@@ -304,8 +304,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
 #pragma unroll
       for (int c = 0; c < NB; ++c) {
         word[c] = __builtin_amdgcn_ballot_w64(lane + 64 * c < f.d && v[c] >= 0.f);
-        // (past d the sums are of zeros only while every scale is finite)
-        l1 += lane + 64 * c < f.d ? fabsf(v[c]) : 0.f;
+        // (past d, which is more than half the columns, the sums are of zeros only
+        // while every scale is finite)
+        l1 += c < NB / 2 || lane + 64 * c < f.d ? fabsf(v[c]) : 0.f;
       }
       l1 = wave_sum(l1);
       if constexpr (NX == 4) {
@@ -375,7 +376,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
       while (empty != 0) {
         const int i = __builtin_ctzll(empty);
         empty &= empty - 1;
-        finish(i, zero4);
+        finish(i, zero4, true);
       }
       struct Tile {  // gathered
         uint32_t f[KS];  // lane: sign dwords half KS .. of matrix row lane & 31
@@ -532,7 +533,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
             if ((ahead >> i) & 1)
               store_partial<NB>(head + w * dpad + NB * lane, sum);
             else
-              finish(i, sum);
+              finish(i, sum, false);
           } while (todo != 0);
         }
         cur = nxt;
