@@ -936,6 +936,16 @@ def test_bgemm_q8_tile_edges(dev, M, N, K):
     test_bgemm_q8_matches_oracle(dev, M, N, K)
 
 
+# The same edges with as many rows as the matrix-core GEMM is taken from (10000
+# up to 128 inputs, 12288 beyond) and with one row less.
+@pytest.mark.parametrize("M,N,K", [(9999, 256, 64), (10000, 256, 64), (10001, 65, 1),
+                                   (10015, 128, 63), (10016, 129, 65), (12287, 96, 256),
+                                   (12288, 96, 256), (12289, 97, 257), (12319, 256, 640),
+                                   (12300, 255, 641), (12290, 128, 1280), (12290, 127, 1281)])
+def test_bgemm_q8_tile_edges_of_many_rows(dev, M, N, K):
+    test_bgemm_q8_matches_oracle(dev, M, N, K)
+
+
 _SIGN_GRAPHS = {}
 
 
