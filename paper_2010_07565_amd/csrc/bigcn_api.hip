@@ -131,16 +131,12 @@ bool sign_layer(int64_t n, int64_t nnz, const bigcn_layer* layers, int32_t nl, i
 
 // What layer l's aggregation leaves of layer l+1's input (the kinds of
 // bigcn::FusedNext): packed signs (4) if layer l+1's aggregation gathers those
-// or its products come from the matrix-core GEMM (wide layers: forming 65-256
-// products of a row by bit counts in the epilogue takes longer than the GEMM,
-// which is bound by writing them), else its products (1); 0: nothing.
+// or if the GEMM forms wide products faster, else its products (1); 0: nothing.
 int fuse_kind(int64_t n, int64_t nnz, const bigcn_layer* layers, int32_t nl, int32_t l) {
   if (!fuses_next(n, nnz, layers, nl, l)) return 0;
   const bigcn_layer& b = layers[l + 1];
-  return sign_layer(n, nnz, layers, nl, l + 1) ||
-                 bigcn::bgemm_q8_e2m1_supported(n, b.d_out, b.d_in)
-             ? 4
-             : 1;
+  if (sign_layer(n, nnz, layers, nl, l + 1)) return 4;
+  return b.d_out <= 64 || bigcn::wide_products_in_epilogue(n, nnz, b.d_in, b.d_out) ? 1 : 4;
 }
 
 // Row stride (bytes of codes, or halves of exact products) of the 8-bit

@@ -110,6 +110,9 @@ struct FusedNext {
   uint64_t* Fn;           // kind 4
   int64_t ldFn;
 };
+// Whether a layer of d > 64 outputs forms the products of a next one of 65-256
+// outputs dn in its epilogue (kind 1) rather than leave its signs (kind 4).
+bool wide_products_in_epilogue(int64_t n, int64_t nnz, int32_t d, int32_t dn);
 // Layers whose self term kind 3 can form: the wide 8-bit aggregation (65-256
 // outputs) with the self weights' words per lane, ceil(kin / 64) times
 // q8_lane_bytes(d), at most 16 (kin <= 256 for 129-256 outputs, <= 512 for

@@ -2408,6 +2408,26 @@ bool q8_supported(int64_t n, int32_t N, int32_t K) {
   return (uint64_t)n * row <= 0xFFFFFFFFull && (uint64_t)n * row * 2u <= 0xFFFFFFFFull;
 }
 
+// Products formed by bit counts cost a row ceil(d / 64) words for each of d'
+// columns; signs and a GEMM cost a launch of 2-6 us.  Products against signs and
+// GEMM (us, whole passes; nodes, entries):
+//   d, d' <= 128 (a lane's weights in four registers): 100 -> 128 -> 128 -> 128: 1 K, 4 K
+//     32.5 / 36.6; 10 K, 250 K 86 / 92; 120 K, 960 K 205 / 211; 400 K, 1.6 M 448 / 451; but
+//     5 K, 500 K 129 / 127 and 2 K, 400 K 95.5 / 95.1, where chunk ends finish most rows
+//   one of them wider: 100 -> 65 -> 200: 2 K, 50 K 33.4 / 35.1; 10 K, 250 K 61.6 / 63.2;
+//     20 K, 240 K 65.8 / 66.1; 20 K, 500 K 98.7 / 97.5; 60 K, 300 K 101 / 99.5
+//   both: 100 -> 200 -> 200 -> 200: 2 K, 50 K 55 / 57; 5 K, 125 K 77 / 79; 5 K, 25 K 67 / 64;
+//     10 K, 250 K 99.7 / 99.1; 20 K, 500 K 166 / 156; 400 K, 1.6 M 648 / 581
+// After a narrow layer signs are faster throughout (100 -> 40 -> 256: 2 K, 10 K 34 / 28).
+bool wide_products_in_epilogue(int64_t n, int64_t nnz, int32_t d, int32_t dn) {
+  constexpr int64_t few = 1 << 18;
+  if (d <= 64) return false;
+  const int words = q8_lane_bytes(d) * q8_lane_bytes(dn);
+  if (words <= 4) return nnz < few || nnz < 64 * n;
+  if (words == 8) return nnz < few && n < 16384;
+  return nnz < few && n <= 6000 && nnz >= 10 * n;
+}
+
 hipError_t launch_bgemm_q8(const uint64_t* F, int64_t M, int64_t ldf,
                            const uint64_t* B, int32_t N, int64_t ldb, int32_t K,
                            int8_t* C8, int64_t ldc8, void* C16, int64_t ldc16,
@@ -2517,7 +2537,10 @@ hipError_t spmm_q8_nb(int64_t n, int64_t nnz, const int64_t* rowptr,
   if constexpr (NB >= 2) {
     if (fn.kind == 3) BIGCN_Q8S(3, 16 / NB);  // NBN: the self weights' words per lane
   }
-  // next products are formed in the epilogue for up to 64 columns
+  if constexpr (NB >= 2) {  // (a narrow layer leaves signs for a wide one)
+    if (q8_lane_bytes(fn.d_out) == 2) BIGCN_Q8S(1, 2);
+    if (q8_lane_bytes(fn.d_out) == 4) BIGCN_Q8S(1, 4);
+  }
   if (q8_lane_bytes(fn.d_out) != 1) return hipErrorInvalidValue;
   BIGCN_Q8S(1, 1);
 #undef BIGCN_Q8S

@@ -924,6 +924,43 @@ def test_fused_pack_gemm_matches_chained(dev, dims):
         assert bool((gs[[3, 500, 1199]] < 0).all())
 
 
+@pytest.mark.parametrize("norm", ["sym", "mean"])
+@pytest.mark.parametrize("dims", [[100, 65, 128, 97, 7], [100, 128, 200, 9], [100, 200, 66, 129],
+                                  [70, 256, 256, 130], [70, 40, 256], [70, 3, 130], [130, 7, 96, 5],
+                                  [70, 16, 200], [33, 31, 65], [100, 64, 256, 7]])
+@pytest.mark.parametrize("size", ["few", "short", "long", "many"])
+def test_wide_layers_in_a_row_match_chained(dev, size, dims, norm):
+    """What a layer leaves a next one of 65-256 outputs, its products or its
+    signs, by size: up to 2^18 entries, 16384 nodes and 64 entries a row for two
+    wide layers (fewer where both are wider than 128), signs after a layer of
+    at most 64; each bit for bit the chained entry points, in both source orders,
+    also for a next row that has the signs of a weight column (|dot| = 256 does
+    not fit the 8-bit code)."""
+    n, und = {"few": (300, 400), "short": (5001, 33_000), "long": (900, 13_000),
+              "many": (16_411, 140_000)}[size]
+    g = workloads.rmat_graph(n, und, 11)
+    rng = np.random.default_rng(sum(dims) + n)
+    L = len(dims) - 1
+    xt = _t(rng.standard_normal((n, dims[0])).astype(np.float32), dev)
+    wts = [workloads.glorot_t(dims[i], dims[i + 1], rng) for i in range(L)]
+    bs = [rng.uniform(-0.1, 0.1, dims[i + 1]).astype(np.float32) for i in range(L)]
+    rowptr_t, colidx_t = _t(g.rowptr, dev), _t(g.colidx, dev)
+    h, hs = xt, []
+    for l in range(L):
+        if l > 0:
+            wts[l][-1] = h[n // 2].cpu().numpy()
+        h, *_ = gpu_layer(dev, g, norm, None, wts[l], bs[l], rowptr_t=rowptr_t,
+                          colidx_t=colidx_t, ht=h)
+        hs.append(h)
+    for so in (False, True):
+        model = bg.BiGCN(rowptr_t, colidx_t, wts, bs, norm=norm, device=dev, source_order=so)
+        assert torch.equal(model.forward(xt), h)
+        hidden = [torch.full((n, d), np.nan, device=dev) for d in dims[1:-1]]
+        assert torch.equal(model.forward(xt, hidden=hidden), h)
+        for a, b in zip(hidden, hs):
+            assert torch.equal(a, b)
+
+
 # ------------------------------------ sign products on the matrix cores
 
 # Row tiles of 32 with remainders, 32-column tiles with remainders, the last
