@@ -259,8 +259,9 @@ bigcn_status bigcn_spmm_csr_sage_q8(int64_t n, int64_t nnz, const int64_t* rowpt
  *   G     = gout, masked by 1[out > 0] when act is RELU
  *   db    = sum_i G_i                       dζ = Ã^T G
  *   dW~   = H~^T dζ,   H~ = diag(β) sign(H) (Eqs. (7)-(8))
- *           (formed as (Ã H~)^T G where dh, dh_tilde and dzeta are NULL and
- *            that reads less: the same sum in another order)
+ *           (formed as (Ã H~)^T G where dh, dh_tilde and dzeta are NULL, that
+ *            reads less and the workspace has the room: the same sum in
+ *            another order)
  *   dH~   = dζ W~^T,   W~ = sign(W) diag(α) (Eqs. (3)-(4))
  *   dH    = dH~ * 1[|dH~| < 1]              (Eq. (14), the indicator taken
  *                                            on |dH~| as printed)
@@ -284,7 +285,11 @@ bigcn_status bigcn_spmm_csr_sage_q8(int64_t n, int64_t nnz, const int64_t* rowpt
  *   dwt_tilde [d_out][lddwt] fp32 dL/dW~ (W^T layout), db fp32[d_out],
  *          dzeta [n][lddz] fp32 dL/dζ: each nullable
  *   workspace  bigcn_layer_backward_workspace_bytes(n, nnz, d_in, d_out)
- *          bytes, 256-byte aligned; contents on entry are ignored.
+ *          bytes, 256-byte aligned; contents on entry are ignored.  The size
+ *          is what either order of dW~ takes at most (up to 4 bytes more per
+ *          node and input than dζ's order needs); a call with less room than
+ *          (Ã H~)^T G needs takes dζ's order, and one with less than that
+ *          needs fails.
  * Sums over nodes (db, dW~) are formed in fp64 over fixed chunks of rows
  * and added in a fixed order; every result is reproducible bit for bit.
  * Errors: EINVAL (bad sizes, NULL required pointers, short leading

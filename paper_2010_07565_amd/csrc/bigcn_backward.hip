@@ -695,8 +695,8 @@ struct BwdLayout {
   int64_t kw, ldm, R, chunks, Rdb, chunks_db;
   int ntw, kgw, jtw, nth, kgh;
   // dW~ from Ã H~ (signs_first), in the place of Gm and dζ (made large enough
-  // for it): packed signs (rows of ldxf words), ones, Ã H~ (rows of ldx) and the
-  // aggregation's plan (of width dx).
+  // for it where the layout is asked for with signs): packed signs (rows of ldxf
+  // words), ones, Ã H~ (rows of ldx) and the aggregation's plan (of width dx).
   int64_t ldxf, ldx;
   int32_t dx;
   size_t off_xf, off_x1, off_x, off_xspmm;
@@ -704,7 +704,7 @@ struct BwdLayout {
       off_spmm, bytes;
 };
 
-BwdLayout bwd_layout(int64_t n, int64_t nnz, int32_t d_in, int32_t d_out) {
+BwdLayout bwd_layout(int64_t n, int64_t nnz, int32_t d_in, int32_t d_out, bool signs) {
   BwdLayout L;
   L.kw = words(d_in);
   L.ldm = (d_out + 3) / 4 * 4;
@@ -745,7 +745,7 @@ BwdLayout bwd_layout(int64_t n, int64_t nnz, int32_t d_in, int32_t d_out) {
   L.off_x1 = L.off_xf + up256((size_t)n * L.ldxf * 8);
   L.off_x = L.off_x1 + up256((size_t)L.dx * 4);
   L.off_xspmm = L.off_x + up256((size_t)n * L.ldx * 4);
-  if (signs_first(n, nnz, d_in, d_out))
+  if (signs)
     off = std::max(off, up256(L.off_xspmm + bigcn::spmm_plan(n, nnz, L.dx).bytes));
   L.off_pdb = off;
   off += up256((size_t)L.chunks_db * d_out * 8);
@@ -807,7 +807,7 @@ extern "C" {
 size_t bigcn_layer_backward_workspace_bytes(int64_t n, int64_t nnz, int32_t d_in,
                                             int32_t d_out) {
   if (n < 0 || nnz < 0 || d_in < 1 || d_out < 1) return 0;
-  return bwd_layout(n, nnz, d_in, d_out).bytes;
+  return bwd_layout(n, nnz, d_in, d_out, signs_first(n, nnz, d_in, d_out)).bytes;
 }
 
 bigcn_status bigcn_layer_backward(int64_t n, int64_t nnz, const int64_t* rowptr,
@@ -845,9 +845,19 @@ bigcn_status bigcn_layer_backward(int64_t n, int64_t nnz, const int64_t* rowptr,
       !aligned(dwt_tilde, 4) || !aligned(db, 4) || !aligned(dzeta, 4) ||
       !aligned(slot, 4) || !aligned(colslot, 4))
     return BIGCN_EALIGN;
-  const BwdLayout L = bwd_layout(n, nnz, d_in, d_out);
+  const bool relu = act == BIGCN_ACT_RELU;
+  BwdLayout L = bwd_layout(n, nnz, d_in, d_out, false);
   if (workspace == nullptr || ws_bytes < L.bytes) return BIGCN_EWORKSPACE;
   if (!aligned(workspace, 256)) return BIGCN_EALIGN;
+  // dW~ from the signs where nothing needs dζ and the workspace has the room
+  constexpr int64_t kRowMax = 1 << 24;  // 16 rows within k_bwd_wtilde_f32's buffer offsets
+  bool x_path = dh == nullptr && dh_tilde == nullptr && dzeta == nullptr &&
+                signs_first(n, nnz, d_in, d_out) && ldg <= kRowMax && (!relu || ldo <= kRowMax);
+  if (x_path) {
+    const BwdLayout Lx = bwd_layout(n, nnz, d_in, d_out, true);
+    x_path = ws_bytes >= Lx.bytes;
+    if (x_path) L = Lx;
+  }
   hipStream_t s = (hipStream_t)stream;
   char* ws = (char*)workspace;
   uint64_t* F = (uint64_t*)(ws + L.off_F);
@@ -889,11 +899,6 @@ bigcn_status bigcn_layer_backward(int64_t n, int64_t nnz, const int64_t* rowptr,
     if (e != hipSuccess) return BIGCN_EHIP; \
   } while (0)
 
-  const bool relu = act == BIGCN_ACT_RELU;
-  constexpr int64_t kRowMax = 1 << 24;  // 16 rows within k_bwd_wtilde_f32's buffer offsets
-  const bool x_path = dh == nullptr && dh_tilde == nullptr && dzeta == nullptr &&
-                      signs_first(n, nnz, d_in, d_out) && ldg <= kRowMax &&
-                      (!relu || ldo <= kRowMax);
   if (x_path) {
     uint64_t* xf = (uint64_t*)(ws + L.off_xf);
     float* x1 = (float*)(ws + L.off_x1);

@@ -265,6 +265,52 @@ def test_weight_gradient_alone_is_as_precise(dev, n, m, d_in, d_out, norm):
     assert err[1] <= 1.1 * err[0]
 
 
+def test_weight_gradient_alone_with_less_workspace(dev):
+    """Room for dζ's order alone is enough for every call: the one that would sum
+    the signs takes dζ's order then (its bits) and leaves the rest untouched."""
+    n, d_in, d_out = 2708, 64, 40
+    g = workloads.rmat_graph(n, 5278, 5)
+    rng = np.random.default_rng(3)
+    rowptr, colidx = _t(g.rowptr, dev), _t(g.colidx, dev)
+    h = _t(rng.standard_normal((n, d_in)).astype(np.float32), dev)
+    wt = _t((rng.standard_normal((d_out, d_in)) * 0.1).astype(np.float32), dev)
+    G = _t((rng.standard_normal((n, d_out)) * 0.05).astype(np.float32), dev)
+    wbits, alpha = bg.pack_weights(wt)
+    full = bg.layer_backward_workspace_bytes(n, g.nnz, d_in, d_out)
+    ws = torch.zeros(full, dtype=torch.uint8, device=dev)
+
+    def run(size, dzeta):
+        dwt = torch.empty((d_out, d_in), device=dev)
+        db = torch.empty(d_out, device=dev)
+        bg.bigcn_layer_backward(rowptr, colidx, h, wt, wbits, alpha, G, dwt, ws[:size], "sym",
+                                db=db, dzeta=dzeta)
+        torch.cuda.synchronize()
+        return dwt, db
+
+    def least(dzeta):
+        lo, hi = 0, full
+        while lo < hi:
+            mid = (lo + hi) // 2
+            try:
+                run(mid, dzeta)
+                hi = mid
+            except bg.BigcnError as e:
+                assert e.status == -3
+                lo = mid + 1
+        return lo
+
+    dzeta = torch.empty((n, d_out), device=dev)
+    size = least(dzeta)
+    assert size < full and least(None) == size
+    ref = run(full, dzeta)
+    ws.fill_(77)
+    got = run(size, None)
+    assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+    assert bool((ws[size:] == 77).all())
+    other = run(full, None)
+    assert not torch.equal(other[0], ref[0]) and torch.equal(other[1], ref[1])
+
+
 @pytest.mark.parametrize("n,d_in,d_out", [(70001, 3, 2), (70001, 17, 33), (5000, 65, 7),
                                           (257, 1, 1), (20011, 256, 3)])
 def test_gradient_sums_over_chunks(dev, n, d_in, d_out):
