@@ -31,6 +31,15 @@ def test_library_exports_every_declared_function():
         assert hasattr(lib, name), name
 
 
+def test_package_exports_what_the_performance_cases_use():
+    """perf/cases.py goes through the package's public names."""
+    text = open(os.path.join(ROOT, "perf", "cases.py")).read()
+    names = set(re.findall(r"\bbg\.(\w+)", text))
+    assert "ITYPE_DTYPES" in names
+    assert names <= set(bg.__all__), names - set(bg.__all__)
+    assert all(hasattr(bg, name) for name in bg.__all__)
+
+
 def test_status_strings():
     lib = bg.load()
     for st in (0, -1, -2, -3, -4, -5):
