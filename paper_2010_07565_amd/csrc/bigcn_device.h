@@ -239,7 +239,7 @@ struct NextLayer {
   int64_t ldF;            // (r = slot[r] when slot is given)
   int32_t kin;            // NX == 3: the layer's input width
   uint64_t* Fn;           // NX == 4: the next layer's packed signs [n][ldFn],
-  int64_t ldFn;           // ldFn <= NB words (pad words are written as zero)
+  int64_t ldFn;           // ldFn words (NB, or 2 where NB is 1: the pad word is zero)
 };
 
 // The next layer's weights as finish_row reads them.
@@ -459,10 +459,9 @@ __device__ inline void finish_row(int64_t r, int64_t deg, const float4_t acc,
   float sc = l1 / (float)fa.d;
   if (nx.sym) sc = sc * (deg > 0 ? 1.0f / sqrtf((float)deg) : 0.f);
   if constexpr (NX == 4) {
-    uint64_t mine = word[0];  // lane w: word w
+    uint64_t mine = 0;  // lane w: word w (the pad word of a narrow row stays zero)
 #pragma unroll
-    for (int c = 1; c < NB; ++c)
-      if (lane == c) mine = word[c];
+    for (int c = 0; c < NB; ++c) mine = lane == c ? word[c] : mine;
     store_words(nx.Fn + dst * nx.ldFn, (uint32_t)nx.ldFn, lane, mine);
     store_first(nx.g + dst, lane, sc);
     return;

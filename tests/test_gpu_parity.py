@@ -961,6 +961,35 @@ def test_wide_layers_in_a_row_match_chained(dev, size, dims, norm):
             assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("dims", [[64, 64, 100], [65, 33, 200, 7], [130, 20, 40]])
+def test_narrow_layers_of_the_largest_graphs_match_chained(dev, dims):
+    """From 2^31 entries on, layers of at most 64 outputs take the wave-per-chunk
+    aggregation too; what it leaves of a wide or narrow next layer equals the
+    chained entry points, which aggregate with the same kernel but pack apart."""
+    n, deg = 1 << 16, (1 << 15) + 1
+    nnz = n * deg
+    gen = torch.Generator(device=dev).manual_seed(sum(dims))
+    rowptr_t = torch.arange(n + 1, device=dev) * deg
+    colidx_t = torch.randint(0, n, (nnz,), dtype=torch.int32, device=dev, generator=gen)
+    rng = np.random.default_rng(sum(dims))
+    xt = torch.randn((n, dims[0]), device=dev, generator=gen)
+    L = len(dims) - 1
+    wts = [workloads.glorot_t(dims[i], dims[i + 1], rng) for i in range(L)]
+    bs = [rng.uniform(-0.1, 0.1, dims[i + 1]).astype(np.float32) for i in range(L)]
+    graph = workloads.Graph(n, np.arange(n + 1) * deg, np.empty(0, dtype=np.int32))
+    h, hs = xt, []
+    for l in range(L):
+        h, *_ = gpu_layer(dev, graph, "mean", None, wts[l], bs[l], rowptr_t=rowptr_t,
+                          colidx_t=colidx_t, ht=h)
+        hs.append(h)
+    model = bg.BiGCN(rowptr_t, colidx_t, wts, bs, norm="mean", device=dev, source_order=False)
+    hidden = [torch.full((n, d), np.nan, device=dev) for d in dims[1:-1]]
+    assert torch.equal(model.forward(xt), h)
+    assert torch.equal(model.forward(xt, hidden=hidden), h)
+    for a, b in zip(hidden, hs):
+        assert torch.equal(a, b)
+
+
 # ------------------------------------ sign products on the matrix cores
 
 # Row tiles of 32 with remainders, 32-column tiles with remainders, the last
