@@ -162,9 +162,10 @@ __device__ inline void stage_weights(uint64_t* sB, const uint64_t* __restrict__ 
 }
 
 // a + b where b may be a product: b is rounded first (no fused multiply-add),
-// so that the self term of a two-weight layer is the same whichever kernel adds
-// it.  (A select between the product and the sum did not keep the compiler from
-// contracting them in every kernel.)
+// so that the self term of a two-weight layer of 65-256 outputs is the same
+// whichever kernel adds it (up to 64 outputs one kernel does, finish_slot, which
+// may contract it).  (A select between the product and the sum did not keep the
+// compiler from contracting them in every kernel.)
 __device__ inline float add_rounded(float a, float b) {
 #pragma clang fp contract(off)
   return a + b;

@@ -1,5 +1,9 @@
 """Shared helpers of the GPU parity tests (comparison rules, sampling)."""
+import ctypes
+
 import numpy as np
+
+import paper_2010_07565_amd as bg
 
 # Floating-point bar: the layer output may differ from the oracle's exact
 # (double precision) value by at most 1e-5 of the mass of the summed terms,
@@ -40,3 +44,14 @@ def sample_rows(g, k, seed, extra_top=3):
     top = np.argsort(deg)[-extra_top:]
     ids = np.concatenate([[0, g.n - 1], top, rng.choice(g.n, size=min(k, g.n), replace=False)])
     return np.unique(ids).astype(np.int64)
+
+
+def gathers_signs(n, nnz, dims, layer, sage=False):
+    """Whether the forward's aggregation of this layer gathers packed signs: the
+    library's own rule (bigcn::sign_supported), for a model of these widths all of
+    whose layers are on the 8-bit path."""
+    rule = bg.load()._ZN5bigcn14sign_supportedElliibb
+    rule.restype = ctypes.c_bool
+    rule.argtypes = [ctypes.c_int64] * 2 + [ctypes.c_int32] * 2 + [ctypes.c_bool] * 2
+    fused = not sage and layer + 2 < len(dims)
+    return rule(n, nnz, dims[layer + 1], dims[layer], sage, fused)

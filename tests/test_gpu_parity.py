@@ -12,7 +12,7 @@ import torch
 import oracle
 import workloads
 import paper_2010_07565_amd as bg
-from helpers import TOL, mass_error, plain_rel_error, u64
+from helpers import TOL, gathers_signs, mass_error, plain_rel_error, u64
 
 pytestmark = pytest.mark.gpu
 
@@ -1035,7 +1035,9 @@ def _sign_graph(kind):
 @pytest.mark.parametrize("kind,norm,act,dims", [
     ("small", "sym", "none", [1, 65]), ("small", "mean", "relu", [63, 128, 40]),
     ("small", "sym", "none", [64, 256, 256, 7]), ("small", "mean", "none", [127, 129, 200, 3]),
-    ("small", "sym", "relu", [128, 193]), ("holes", "mean", "none", [100, 256, 47]),
+    ("small", "sym", "relu", [128, 193]), ("large", "sym", "relu", [128, 193]),
+    ("large", "mean", "none", [127, 193]), ("small", "mean", "none", [100, 63, 200, 5]),
+    ("small", "sym", "relu", [70, 7, 96]), ("holes", "mean", "none", [100, 256, 47]),
     ("holes", "sym", "relu", [65, 127, 128, 65]), ("holes", "sym", "none", [100, 200, 256, 7]),
     ("large", "mean", "relu", [129, 65]),
     ("large", "sym", "none", [256, 128, 128, 40]), ("large", "mean", "none", [255, 97, 5])])
@@ -1045,6 +1047,11 @@ def test_forward_over_signs_equals_chained(dev, kind, norm, act, dims):
     points, which gather ready products.  Two feature rows have the signs of
     a weight column (the largest products)."""
     g = _sign_graph(kind)
+    # (unfused layers of 129 and more outputs take more entries than "small" has;
+    # layers of at most 64 outputs gather codes and leave signs)
+    signs = [gathers_signs(g.n, g.nnz, dims, l) for l in range(len(dims) - 1)]
+    assert any(signs) or (kind, dims) == ("small", [128, 193])
+    assert signs[0] or dims[1] <= 64 or dims == [128, 193]
     rng = np.random.default_rng(sum(dims))
     L = len(dims) - 1
     x = rng.standard_normal((g.n, dims[0])).astype(np.float32)
@@ -1078,6 +1085,7 @@ def test_forward_over_signs_when_a_scale_overflows(dev, dims):
     and, for a single layer, a weight column (rows without entries still give
     the bias)."""
     g = _sign_graph("holes")
+    assert gathers_signs(g.n, g.nnz, dims, 0)
     rng = np.random.default_rng(sum(dims))
     L, K = len(dims) - 1, dims[0]
     x = rng.standard_normal((g.n, K)).astype(np.float32)
@@ -1110,6 +1118,7 @@ def test_forward_over_signs_when_a_scale_overflows(dev, dims):
 @pytest.mark.parametrize("dims", [[100, 256, 47], [65, 65, 128], [200, 128, 9]])
 def test_sage_forward_over_signs_equals_chained(dev, dims):
     g = workloads.without_self_loops(_sign_graph("large"))
+    assert gathers_signs(g.n, g.nnz, dims, 0, sage=True)
     rng = np.random.default_rng(sum(dims))
     L = len(dims) - 1
     xt = _t(rng.standard_normal((g.n, dims[0])).astype(np.float32), dev)
