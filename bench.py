@@ -19,12 +19,20 @@ Prints one JSON line.  Besides the forward-pass throughput it carries
    (HIP events around a graph replay of --kernel-reps back-to-back calls on
    the launch stream); an aggregation step is all of its kernels (one for
    layers of at most 64 columns, aggregation and fix-up for wider 8-bit
-   layers, plus a row plan on the exact-product path);
- - "roofline": the dominant kernel (largest share of a forward pass) against
-   its bound: HBM bytes for pack / aggregation (each array counted once;
-   the aggregation entries also carry the gather model, every edge reading
-   its source's whole product row), bit operations on the vector ALUs for
-   the binary GEMM; "traffic" is the counter-measured HBM bytes of that call
+   layers, plus a row plan on the exact-product path).  A layer whose
+   aggregation gathers packed signs in the pass ("spmm_sign") has no entry
+   point of its own: its time is that of a forward pass over the layer (and
+   the next, where only a fused layer gathers signs) less its other steps.
+   "in_pass" is whether the forward pass launches the step: a fused layer
+   leaves the next one's signs or products, so its pack, or pack and GEMM, are
+   not launched;
+ - "roofline": the dominant kernel (largest share of a forward pass, among
+   those it launches) against its bound: HBM bytes for pack / aggregation
+   (each array counted once; the aggregation entries also carry the gather
+   model, every edge reading its source's whole row), sign products per second
+   for the binary GEMM and the aggregation of signs, against the vector ALUs'
+   bit operations or the matrix cores' 4-bit products, whichever it runs on;
+   "traffic" is the counter-measured HBM bytes of that call
    (profiles/hbm_traffic_<workload>.md) while the kernel sources match, and
    "traffic_gbs" / "traffic_frac" those bytes over the call's average time
    (against 8 TB/s);
@@ -69,6 +77,8 @@ HBM_PEAK_GBS = 8000.0
 VALU_BITOP_PEAK = 256 * 4 * 16 * 2.4e9 * 16
 # Dense int8 MFMA: 5.0 P ops/s = 2.5 P multiply-adds/s, one sign product each.
 MFMA_I8_BITOP_PEAK = 2.5e15
+# Dense 4-bit floats: twice that (32 x 32 x 64 products in 32 cycles of a SIMD).
+MFMA_E2M1_BITOP_PEAK = 5.0e15
 METRIC = "nodes/sec full Bi-GCN forward; bGEMM bit-ops/s; SpMM/pack HBM GB/s vs peak"
 COPY_BYTES = 256 << 20   # calibration copy of the byte counters
 
@@ -151,6 +161,13 @@ def time_cold(fn, reps, torch, flush):
     return total / reps * 1e-3
 
 
+def gemm_peak(q8, n, d, K, bg):
+    """Peak sign products per second of the unit a binary GEMM step runs on."""
+    if q8:
+        return MFMA_E2M1_BITOP_PEAK if bg._lib.gemm_on_matrix_cores(n, d, K) else VALU_BITOP_PEAK
+    return MFMA_I8_BITOP_PEAK if n >= 65536 and K >= 256 and d <= 256 else VALU_BITOP_PEAK
+
+
 def bgemm_ab(shapes, reps, torch, bg, dev):
     """Both binary-GEMM algorithms on each (M, N, K): seeded random sign bits
     (pad bits zero), results compared bit for bit, durations from time_calls."""
@@ -186,7 +203,8 @@ def bgemm_ab(shapes, reps, torch, bg, dev):
 def measured_traffic(workload_name, layer, entry):
     """HBM bytes (read + written) of one entry-point call, from the committed
     counter summary profiles/hbm_traffic_<workload>.md, or None when there is
-    none or the kernel / launch sources changed since it was taken."""
+    none or the kernel / launch sources changed since it was taken (every device
+    source of the forward pass that is there)."""
     import hashlib
     import re
     path = os.path.join(ROOT, "profiles", "hbm_traffic_%s.md" % workload_name)
@@ -197,9 +215,12 @@ def measured_traffic(workload_name, layer, entry):
         return None
     rec = json.loads(m.group(1))
     h = hashlib.sha256()
-    for src in ("bigcn_kernels.hip", "bigcn_api.hip"):
-        with open(os.path.join(ROOT, "paper_2010_07565_amd", "csrc", src), "rb") as f:
-            h.update(f.read())
+    for src in ("bigcn_kernels.hip", "bigcn_api.hip", "bigcn_e2m1.hip", "bigcn_device.h",
+                "bigcn_internal.h"):
+        src = os.path.join(ROOT, "paper_2010_07565_amd", "csrc", src)
+        if os.path.exists(src):
+            with open(src, "rb") as f:
+                h.update(f.read())
     if rec.get("sources_sha256") != h.hexdigest():
         return None
     for e in rec["entries"]:
@@ -276,10 +297,34 @@ def to_source_order(order, *ts):
             t.copy_(t[order])
 
 
+def sign_pass(w, model, l, h, m0, r0, rowptr, colidx, torch, bg, dev):
+    """A forward pass over layer l, which gathers packed signs, and over the next
+    too where only a fused layer does: (call, layer l's output, layers in it)."""
+    g = w.graph
+    K, d = model.layers[l].d_in, model.layers[l].d_out
+    sage = model.layers[l].wbits_self is not None
+    span = 1 if bg._lib.sign_supported(g.n, g.nnz, d, K, sage, False) else 2
+    out = torch.empty((g.n, d), dtype=torch.float32, device=dev)
+
+    def call_of(layers, res):
+        ws = torch.empty(bg.forward_workspace_bytes(g.n, g.nnz, layers), dtype=torch.uint8,
+                         device=dev)
+        return lambda: bg.bigcn_forward(rowptr, colidx, h, layers, res, ws, m0, r0, w.norm,
+                                        slot=model.slot, colslot=model.colslot)
+    one = call_of([model.layers[l]], out)
+    if span == 1:
+        return one, out, 1
+    one()                                  # (the output, by the code aggregation)
+    res = torch.empty((g.n, model.layers[l + 1].d_out), dtype=torch.float32, device=dev)
+    return call_of(model.layers[l:l + 2], res), out, 2
+
+
 def traffic_probe(w, model, x, rowptr, colidx, torch, bg, dev):
     """One eager call of every per-layer entry point, in the order the
-    kernel table times them, then one 256 MiB device copy of known size."""
+    kernel table times them (for a layer that gathers signs the pack and the
+    forward pass of sign_pass), then one 256 MiB device copy of known size."""
     g = w.graph
+    route = bg._lib.forward_route(g.n, g.nnz, model.layers)
     kwmax = max(words(wt.shape[1]) for wt in w.weights_t)
     ldF = (kwmax + 1) // 2 * 2
     F = torch.empty((g.n, ldF), dtype=torch.int64, device=dev)
@@ -301,7 +346,12 @@ def traffic_probe(w, model, x, rowptr, colidx, torch, bg, dev):
         log("probe layer %d: pack" % l)
         bg.bigcn_binarize_pack(h, F[:, :kw], gs, mu_t if l == 0 else None,
                                rstd_t if l == 0 else None, rowptr, w.norm)
-        if bg.q8_supported(g.n, d, K):
+        if route[l]["signs"]:
+            log("probe layer %d: spmm_sign" % l)
+            call, out, _ = sign_pass(w, model, l, h, mu_t if l == 0 else None,
+                                     rstd_t if l == 0 else None, rowptr, colidx, torch, bg, dev)
+            call()
+        elif bg.q8_supported(g.n, d, K):
             W = bg.q8_row(d)
             c8 = C8.view(-1)[:g.n * W].view(g.n, W)
             c16 = C.view(-1)[:g.n * W].view(g.n, W)
@@ -530,6 +580,7 @@ def main():
     kernels = []
     calls = {}
     order, src = source_order(model, torch)
+    route = bg._lib.forward_route(g.n, g.nnz, model.layers)
     h = x
     reps = args.kernel_reps
     for l, ly in enumerate(model.layers):
@@ -544,6 +595,24 @@ def main():
         q8 = bg.q8_supported(g.n, d, K)
         sage = ly.wbits_self is not None
         t_self = None
+        # what the pass launches of this layer: not what the layer before leaves
+        left = route[l - 1]["leaves"] if l > 0 else None
+        if route[l]["signs"]:
+            f_layer, out, span = sign_pass(w, model, l, h, m0, r0, rowptr, colidx, torch, bg, dev)
+            row = bg._lib.sign_row_bytes(K)
+            work = 8 * (g.n + 1) + 4 * g.nnz + 4 * g.n + g.n * row + 4 * g.n * d
+            gather = g.nnz * (8 + row) + g.n * d * 4
+            kernels += [
+                dict(kernel="pack", layer=l, us=t_pack * 1e6, bound="hbm",
+                     achieved=specs[l]["pack_bytes"] / t_pack / 1e9, unit="GB/s",
+                     peak=HBM_PEAK_GBS, work=specs[l]["pack_bytes"], in_pass=left is None),
+                dict(kernel="spmm_sign", layer=l, us=time_calls(f_layer, reps, torch) * 1e6,
+                     bound="alu", unit="Tbitop/s", peak=MFMA_E2M1_BITOP_PEAK / 1e12,
+                     ops=g.nnz * K * d, work=g.nnz * K * d, bytes=work, gather_bytes=gather,
+                     in_pass=True, span=span)]
+            calls[(l, "pack")], calls[(l, "spmm")] = f_pack, f_layer
+            h = out
+            continue
         if q8:
             # the forward keeps these products as 8-bit half-codes, in rows
             # of q8_row(d) entries
@@ -602,11 +671,12 @@ def main():
         kernels += [
             dict(kernel="pack", layer=l, us=t_pack * 1e6, bound="hbm",
                  achieved=s["pack_bytes"] / t_pack / 1e9, unit="GB/s", peak=HBM_PEAK_GBS,
-                 work=s["pack_bytes"]),
+                 work=s["pack_bytes"], in_pass=left is None),
             dict(kernel="bgemm_q8" if q8 else "bgemm", layer=l, us=t_gemm * 1e6, bound="alu",
                  achieved=s["gemm_ops"] / t_gemm / 1e12, unit="Tbitop/s",
-                 peak=VALU_BITOP_PEAK / 1e12, work=s["gemm_ops"], bytes=s["gemm_bytes"],
-                 hbm_gbs=s["gemm_bytes"] / t_gemm / 1e9),
+                 peak=gemm_peak(q8, g.n, d, K, bg) / 1e12, work=s["gemm_ops"],
+                 bytes=s["gemm_bytes"], hbm_gbs=s["gemm_bytes"] / t_gemm / 1e9,
+                 in_pass=left != "products"),
             dict(kernel=("spmm_sage_q8" if sage else "spmm_q8") if q8 else "spmm", layer=l,
                  us=t_spmm * 1e6, bound="hbm",
                  achieved=(s["spmm_bytes"] + (g.n * d * 2 if sage else 0)) / t_spmm / 1e9,
@@ -617,27 +687,41 @@ def main():
                  gather_bytes=g.nnz * (8 + (bg.q8_row(d) if q8 else 2 * ((d + 7) // 8 * 8)))
                  + g.n * d * 4,
                  gather_gbs=(g.nnz * (8 + (bg.q8_row(d) if q8 else 2 * ((d + 7) // 8 * 8)))
-                             + g.n * d * 4) / t_spmm / 1e9),
+                             + g.n * d * 4) / t_spmm / 1e9, in_pass=True),
         ]
         if t_self is not None:
             kernels.append(dict(kernel="bgemm_self", layer=l, us=t_self * 1e6, bound="alu",
                                 achieved=s["gemm_ops"] / t_self / 1e12, unit="Tbitop/s",
                                 peak=VALU_BITOP_PEAK / 1e12, work=s["gemm_ops"],
                                 bytes=g.n * kw * 8 + d * kw * 8 + g.n * d * 2,
-                                hbm_gbs=(g.n * kw * 8 + g.n * d * 2) / t_self / 1e9))
+                                hbm_gbs=(g.n * kw * 8 + g.n * d * 2) / t_self / 1e9,
+                                in_pass=d <= 64))   # (wider: formed in the epilogue)
         h = out
+    us = {(k["layer"], k["kernel"].split("_")[0]): k["us"] for k in kernels
+          if k["kernel"] != "bgemm_self"}
+    for k in kernels:
+        if k["kernel"] == "spmm_sign":     # the layer's pass less its other steps
+            l = k["layer"]
+            k["us"] -= us[(l, "pack")]
+            if k.pop("span") == 2:
+                k["us"] -= us.get((l + 1, "bgemm"), 0.0) + us[(l + 1, "spmm")]
+            k["achieved"] = k.pop("ops") / k["us"] * 1e6 / 1e12
+            k["gather_gbs"] = k["gather_bytes"] / k["us"] * 1e6 / 1e9
     for k in kernels:
         k["frac"] = k["achieved"] / k["peak"]
         log("  L%d %-5s %9.2f us  %8.1f %s  (%.1f%% of peak)" % (
             k["layer"], k["kernel"], k["us"], k["achieved"], k["unit"], 100 * k["frac"]))
-    dom = max(kernels, key=lambda k: k["us"])
+    dom = max((k for k in kernels if k["in_pass"]), key=lambda k: k["us"])
     entry = dom["kernel"].split("_")[0]                  # pack / bgemm / spmm
     traffic = measured_traffic(w.name, dom["layer"], entry)
     # the same entry point with cold caches (inputs from HBM, not from the
     # last-level cache that holds a small graph's whole working set)
-    calls[(dom["layer"], "prep")]()       # that layer's own products, in source order
+    if (dom["layer"], "prep") in calls:   # that layer's own products, in source order
+        calls[(dom["layer"], "prep")]()
     cold_us = time_cold(calls[(dom["layer"], "gemm" if entry == "bgemm" else entry)],
                         COLD_REPS, torch, flush) * 1e6
+    if dom["kernel"] == "spmm_sign":      # (a pass: its other steps come warm after the pack)
+        cold_us -= us[(dom["layer"], "spmm")] - dom["us"]
     cold_achieved = dom["achieved"] * dom["us"] / cold_us
     roofline = dict(kernel="%s (layer %d)" % (dom["kernel"], dom["layer"]), bound=dom["bound"],
                     achieved=round(dom["achieved"], 2), peak=dom["peak"], unit=dom["unit"],

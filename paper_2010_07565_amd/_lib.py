@@ -382,6 +382,54 @@ def _layers(layers: Sequence[Layer]):
     return arr
 
 
+def _rule(name: str, argtypes, *args) -> bool:
+    """One of the library's own size rules (a C++ function of namespace bigcn)."""
+    fn = getattr(load(), name)
+    fn.restype, fn.argtypes = ctypes.c_bool, argtypes
+    return fn(*args)
+
+
+def sign_supported(n: int, nnz: int, d: int, K: int, two_weight: bool, fused: bool) -> bool:
+    """Whether the forward's aggregation of an 8-bit layer gathers packed signs."""
+    return _rule("_ZN5bigcn14sign_supportedElliibb",
+                 [_i64, _i64, _i32, _i32, ctypes.c_bool, ctypes.c_bool],
+                 n, nnz, d, K, two_weight, fused)
+
+
+def sign_row_bytes(K: int) -> int:
+    """Bytes of a node's packed signs where an aggregation gathers them."""
+    return 16 if K <= 128 else 32
+
+
+def gemm_on_matrix_cores(n: int, d: int, K: int) -> bool:
+    """Whether bigcn_bgemm_q8 runs on the matrix cores."""
+    return _rule("_ZN5bigcn24bgemm_q8_on_matrix_coresElii", [_i64, _i32, _i32], n, d, K)
+
+
+def forward_route(n: int, nnz: int, layers: Sequence[Layer]):
+    """What bigcn_forward does for each layer: ``signs``, whether its aggregation
+    gathers packed signs, and ``leaves``, what its epilogue forms of the next
+    layer's input ("products", "signs" or None)."""
+    q8 = [q8_supported(n, ly.d_out, ly.d_in) for ly in layers]
+    sage = [ly.wbits_self is not None for ly in layers]
+    fused = [l + 1 < len(layers) and nnz > 0 and not (sage[l] or sage[l + 1])
+             and q8[l] and q8[l + 1] for l in range(len(layers))]
+    signs = [sign_supported(n, nnz, ly.d_out, ly.d_in, sage[l], fused[l])
+             for l, ly in enumerate(layers)]
+
+    def leaves(l):
+        if not fused[l]:
+            return None
+        d, dn = layers[l].d_out, layers[l + 1].d_out
+        if signs[l + 1]:
+            return "signs"
+        if dn <= 64 or _rule("_ZN5bigcn25wide_products_in_epilogueEllii",
+                             [_i64, _i64, _i32, _i32], n, nnz, d, dn):
+            return "products"
+        return "signs"
+    return [dict(signs=signs[l], leaves=leaves(l)) for l in range(len(layers))]
+
+
 def forward_workspace_bytes(n: int, nnz: int, layers: Sequence[Layer]) -> int:
     return load().bigcn_forward_workspace_bytes(n, nnz, _layers(layers), len(layers))
 

@@ -575,7 +575,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
 // 32 x 32 x 64 product takes 32 cycles and the kernel is bound by the codes it
 // writes (2.45 M x 256 x 256: 479 us with bit counts, 226 us here for 627 MB
 // written; 233 K x 256 x 602: 110 -> 42 us; 169 K x 256 x 256: 42 -> 19 us; with
-// few rows the weights' expansion bounds it, see launch_bgemm_q8).  Lane l holds column l & 31 of every 32-column tile, whose bytes
+// few rows the weights' expansion bounds it, see bgemm_q8_on_matrix_cores).  Lane l holds column l & 31 of every 32-column tile, whose bytes
 // fill the interleaved row layout in pieces of 32 lanes: whole 128-byte lines
 // for 129-256 columns.
 template <int NT>

@@ -64,7 +64,8 @@ hipError_t launch_bgemm_q8(const uint64_t* F, int64_t M, int64_t ldf,
                            float* g, hipStream_t stream);
 
 // launch_bgemm_q8 on the matrix cores (e2m1 signs), the same results; taken
-// by launch_bgemm_q8 where it is supported.
+// by launch_bgemm_q8 where bgemm_q8_on_matrix_cores says so.
+bool bgemm_q8_on_matrix_cores(int64_t M, int32_t N, int32_t K);
 bool bgemm_q8_e2m1_supported(int64_t M, int32_t N, int32_t K);
 hipError_t launch_bgemm_q8_e2m1(const uint64_t* F, int64_t M, int64_t ldf, const uint64_t* B,
                                 int32_t N, int64_t ldb, int32_t K, int8_t* C8, int64_t ldc8,

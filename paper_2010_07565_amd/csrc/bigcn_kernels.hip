@@ -2428,19 +2428,22 @@ bool wide_products_in_epilogue(int64_t n, int64_t nnz, int32_t d, int32_t dn) {
   return nnz < few && n <= 6000 && nnz >= 10 * n;
 }
 
+// The matrix cores from 10-12 K rows on: below, a block's expansion of the
+// weights takes longer than its few tiles (popcount against matrix cores, us:
+// 3 K rows 128 x 100 2.8 / 3.3, 256 x 256 4.0 / 5.5, 256 x 640 5.9 / 9.1; 10 K rows
+// 128 x 64 3.3 / 3.0, 256 x 100 4.5 / 4.5, 256 x 256 5.6 / 5.8, 256 x 640 8.8 / 9.4;
+// 30 K rows 5.2 / 3.4, 7.7 / 5.2, 10.3 / 6.6, 17.9 / 10.2).
+bool bgemm_q8_on_matrix_cores(int64_t M, int32_t N, int32_t K) {
+  return M >= (K <= 128 ? 10000 : 12288) && bgemm_q8_e2m1_supported(M, N, K);
+}
+
 hipError_t launch_bgemm_q8(const uint64_t* F, int64_t M, int64_t ldf,
                            const uint64_t* B, int32_t N, int64_t ldb, int32_t K,
                            int8_t* C8, int64_t ldc8, void* C16, int64_t ldc16,
                            float* g, hipStream_t stream) {
   if (M == 0) return hipSuccess;
-  // The matrix cores from 10-12 K rows on: below, a block's expansion of the
-  // weights takes longer than its few tiles (popcount against matrix cores, us:
-  // 3 K rows 128 x 100 2.8 / 3.3, 256 x 256 4.0 / 5.5, 256 x 640 5.9 / 9.1; 10 K rows
-  // 128 x 64 3.3 / 3.0, 256 x 100 4.5 / 4.5, 256 x 256 5.6 / 5.8, 256 x 640 8.8 / 9.4;
-  // 30 K rows 5.2 / 3.4, 7.7 / 5.2, 10.3 / 6.6, 17.9 / 10.2).
   // (its last tile's offsets reach up to 32 rows past the matrix)
-  if (M >= (K <= 128 ? 10000 : 12288) && bgemm_q8_e2m1_supported(M, N, K) &&
-      (uint64_t)(M + 32) * ldc8 <= 0xFFFFFFFFull)
+  if (bgemm_q8_on_matrix_cores(M, N, K) && (uint64_t)(M + 32) * ldc8 <= 0xFFFFFFFFull)
     return launch_bgemm_q8_e2m1(F, M, ldf, B, N, ldb, K, C8, ldc8, C16, ldc16, g, stream);
   constexpr int RM = 4;
   const int nb = q8_lane_bytes(N);

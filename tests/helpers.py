@@ -1,6 +1,4 @@
 """Shared helpers of the GPU parity tests (comparison rules, sampling)."""
-import ctypes
-
 import numpy as np
 
 import paper_2010_07565_amd as bg
@@ -47,11 +45,8 @@ def sample_rows(g, k, seed, extra_top=3):
 
 
 def gathers_signs(n, nnz, dims, layer, sage=False):
-    """Whether the forward's aggregation of this layer gathers packed signs: the
-    library's own rule (bigcn::sign_supported), for a model of these widths all of
-    whose layers are on the 8-bit path."""
-    rule = bg.load()._ZN5bigcn14sign_supportedElliibb
-    rule.restype = ctypes.c_bool
-    rule.argtypes = [ctypes.c_int64] * 2 + [ctypes.c_int32] * 2 + [ctypes.c_bool] * 2
+    """Whether the forward's aggregation of this layer gathers packed signs, by the
+    library's own rule, for a model of these widths all of whose layers are on
+    the 8-bit path."""
     fused = not sage and layer + 2 < len(dims)
-    return rule(n, nnz, dims[layer + 1], dims[layer], sage, fused)
+    return bg._lib.sign_supported(n, nnz, dims[layer + 1], dims[layer], sage, fused)

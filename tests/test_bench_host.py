@@ -52,6 +52,35 @@ def test_measured_traffic_is_dropped_when_kernels_changed(tmp_path, monkeypatch)
     assert bench.measured_traffic("toy", 0, "spmm") is None
 
 
+def test_measured_traffic_is_dropped_when_any_device_source_changed(tmp_path, monkeypatch):
+    # the figures of a pass with sign aggregations depend on their file and headers too
+    sources = [("bigcn_kernels.hip", b"// kernels\n"), ("bigcn_api.hip", b"// api\n"),
+               ("bigcn_e2m1.hip", b"// signs\n"), ("bigcn_device.h", b"// device\n"),
+               ("bigcn_internal.h", b"// internal\n")]
+    _fake_tree(tmp_path, b"// kernels\n", [text for _, text in sources])
+    csrc = tmp_path / "paper_2010_07565_amd" / "csrc"
+    for name, text in sources:
+        (csrc / name).write_bytes(text)
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    assert bench.measured_traffic("toy", 0, "spmm") == 1024
+    for name, text in sources:
+        (csrc / name).write_bytes(text + b"// edited\n")
+        assert bench.measured_traffic("toy", 0, "spmm") is None, name
+        (csrc / name).write_bytes(text)
+
+
+def test_forward_route_follows_the_library():
+    # the products-like model at its size and at a small one: what bench.py ranks
+    import paper_2010_07565_amd as bg
+    layers = [bg.Layer(a, b, None, None) for a, b in ((100, 256), (256, 256), (256, 47))]
+    route = bg._lib.forward_route(2449029, 126149029, layers)
+    assert [r["signs"] for r in route] == [True, False, False]
+    assert [r["leaves"] for r in route] == ["signs", "products", None]
+    route = bg._lib.forward_route(2000, 50000, layers)
+    assert not any(r["signs"] for r in route)
+    assert [r["leaves"] for r in route] == ["products", "products", None]
+
+
 def test_committed_traffic_summaries_parse():
     # every committed summary carries a hash and per-entry byte counts
     import re
