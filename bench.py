@@ -301,9 +301,8 @@ def sign_pass(w, model, l, h, m0, r0, rowptr, colidx, torch, bg, dev):
     """A forward pass over layer l, which gathers packed signs, and over the next
     too where only a fused layer does: (call, layer l's output, layers in it)."""
     g = w.graph
-    K, d = model.layers[l].d_in, model.layers[l].d_out
-    sage = model.layers[l].wbits_self is not None
-    span = 1 if bg._lib.sign_supported(g.n, g.nnz, d, K, sage, False) else 2
+    d = model.layers[l].d_out
+    span = 1 if bg._lib.forward_route(g.n, g.nnz, model.layers[l:l + 1])[0]["signs"] else 2
     out = torch.empty((g.n, d), dtype=torch.float32, device=dev)
 
     def call_of(layers, res):

@@ -389,13 +389,6 @@ def _rule(name: str, argtypes, *args) -> bool:
     return fn(*args)
 
 
-def sign_supported(n: int, nnz: int, d: int, K: int, two_weight: bool, fused: bool) -> bool:
-    """Whether the forward's aggregation of an 8-bit layer gathers packed signs."""
-    return _rule("_ZN5bigcn14sign_supportedElliibb",
-                 [_i64, _i64, _i32, _i32, ctypes.c_bool, ctypes.c_bool],
-                 n, nnz, d, K, two_weight, fused)
-
-
 def sign_row_bytes(K: int) -> int:
     """Bytes of a node's packed signs where an aggregation gathers them."""
     return 16 if K <= 128 else 32
@@ -414,20 +407,18 @@ def forward_route(n: int, nnz: int, layers: Sequence[Layer]):
     sage = [ly.wbits_self is not None for ly in layers]
     fused = [l + 1 < len(layers) and nnz > 0 and not (sage[l] or sage[l + 1])
              and q8[l] and q8[l + 1] for l in range(len(layers))]
-    signs = [sign_supported(n, nnz, ly.d_out, ly.d_in, sage[l], fused[l])
-             for l, ly in enumerate(layers)]
-
-    def leaves(l):
-        if not fused[l]:
-            return None
-        d, dn = layers[l].d_out, layers[l + 1].d_out
-        if signs[l + 1]:
-            return "signs"
-        if dn <= 64 or _rule("_ZN5bigcn25wide_products_in_epilogueEllii",
-                             [_i64, _i64, _i32, _i32], n, nnz, d, dn):
-            return "products"
-        return "signs"
-    return [dict(signs=signs[l], leaves=leaves(l)) for l in range(len(layers))]
+    signs, leaves = [False] * len(layers), [None] * len(layers)
+    for l in reversed(range(len(layers))):    # (a layer's depends on the next one's)
+        d, K = layers[l].d_out, layers[l].d_in
+        if fused[l]:
+            dn = layers[l + 1].d_out
+            leaves[l] = "products" if not signs[l + 1] and (dn <= 64 or _rule(
+                "_ZN5bigcn25wide_products_in_epilogueEllii", [_i64, _i64, _i32, _i32],
+                n, nnz, d, dn)) else "signs"
+        signs[l] = _rule("_ZN5bigcn14sign_supportedElliibi",
+                         [_i64, _i64, _i32, _i32, ctypes.c_bool, _int], n, nnz, d, K, sage[l],
+                         {None: 0, "products": 1, "signs": 4}[leaves[l]])
+    return [dict(signs=s, leaves=f) for s, f in zip(signs, leaves)]
 
 
 def forward_workspace_bytes(n: int, nnz: int, layers: Sequence[Layer]) -> int:

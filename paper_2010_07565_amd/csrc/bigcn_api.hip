@@ -121,12 +121,14 @@ bool fuses_next(int64_t n, int64_t nnz, const bigcn_layer* layers, int32_t nl, i
   return bigcn::q8_supported(n, a.d_out, a.d_in) && bigcn::q8_supported(n, b.d_out, b.d_in);
 }
 
+int fuse_kind(int64_t n, int64_t nnz, const bigcn_layer* layers, int32_t nl, int32_t l);
+
 // Whether layer l's aggregation gathers packed signs and forms the products
 // itself (launch_spmm_sign) instead of gathering ready 8-bit codes.
 bool sign_layer(int64_t n, int64_t nnz, const bigcn_layer* layers, int32_t nl, int32_t l) {
   const bigcn_layer& ly = layers[l];
   return bigcn::sign_supported(n, nnz, ly.d_out, ly.d_in, ly.wbits_self != nullptr,
-                               fuses_next(n, nnz, layers, nl, l));
+                               fuse_kind(n, nnz, layers, nl, l));
 }
 
 // What layer l's aggregation leaves of layer l+1's input (the kinds of

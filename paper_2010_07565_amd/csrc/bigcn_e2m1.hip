@@ -774,27 +774,38 @@ hipError_t launch_bgemm_q8_e2m1(const uint64_t* F, int64_t M, int64_t ldf, const
   return hipGetLastError();
 }
 
-// Where gathering signs is faster than gathering codes (whole one-layer
-// passes, codes against signs, with the GEMM that only codes need):
-//   up to 128 inputs: from 2 M entries (169 K nodes, 2.5 M entries, 100 -> 128:
-//     113 -> 102 us; 60 K nodes, 2.3 M: 82 -> 70 us; the 128 -> 256 layer of
-//     the arxiv-shaped pass, which leaves signs for the next: pass 441 -> 419
-//     us), from 4 M where 256 fp32 columns are written (169 K nodes: 150
-//     -> 157 us; 233 K nodes, 115 M entries: 2.33 -> 1.99 ms; 1.2 M nodes, 11 M:
-//     0.90 -> 0.78 ms).  Below that a launch's few tiles per wave do not pay
-//     for its start (30 K nodes, 0.8 M entries: 65 -> 75 us).  A two-weight
-//     layer's longer epilogue moves this up (169 K nodes: pass 665 -> 702
-//     us; 1.2 M nodes, 60 M entries: 2.28 -> 2.00 ms).
-//   129-256 inputs double the matrix work: up to 128 outputs on large graphs
-//     (60 K nodes, 8.5 M entries, 256 -> 128: 198 -> 174 us; 2.45 M nodes, 200
-//     -> 128: 2.99 -> 2.85 ms; but 169 K nodes, 2.5 M entries 142 -> 155 us);
-//     with 256 outputs codes stay ahead where they fit the last-level cache
-//     (233 K nodes: 2.4 against 2.9 ms) and are level elsewhere.
-bool sign_supported(int64_t n, int64_t nnz, int32_t d, int32_t K, bool two_weight, bool fused) {
+// Where gathering signs is faster than gathering codes (whole passes, codes
+// against signs, with the GEMM that only codes need; nodes, entries):
+//   up to 128 inputs, up to 128 outputs: from 2 M entries (100 -> 128: 169 K, 2.5 M 113 ->
+//     102 us; 60 K, 2.3 M 82 -> 70; 700 K, 2.1 M, three a row, 273 -> 262).  Below that a
+//     launch's few tiles per wave do not pay for its start (30 K, 0.8 M: 65 -> 75).
+//   129-256 outputs: from 4 M where 256 fp32 columns are written (169 K, 2.5 M 150 -> 157;
+//     1.2 M, 5.2 M 711 -> 699; 233 K, 115 M 2330 -> 1990); from 2 M where they leave signs
+//     (128 -> 256 -> 256 -> 40: 169 K, 2.5 M 416 -> 405; 60 K, 2.5 M 298 -> 292; but 65 -> 192
+//     -> 65: 700 K, 2.9 M, four a row, 569 -> 581, 2.4 M, 12 M 2003 -> 1866).  Where they leave
+//     a narrow layer's products, which a tile's long epilogue forms row by row, rows
+//     have to be longer (100 -> 256 -> 47: 700 K, 2.1 M, three a row, 556 -> 622;
+//     1.2 M, 5.2 M 981 -> 1075; 2.4 M, 12 M 2047 -> 2125; 300 K, 3.5 M (12) 371 -> 388, 300 K,
+//     5.3 M (18) 445 -> 440, 1.2 M, 15 M (13) 1413 -> 1383, 60 K, 2.5 M (41) 201 -> 201,
+//     20 K, 2.4 M (120) 130 -> 120)
+//   a two-weight layer's epilogue is longer yet (169 K nodes: pass 665 -> 702; 2.4 M, 9.6 M
+//     (four a row) 100 -> 128 1528 -> 1618; 2.4 M, 28 M (12) 1813 -> 1751; 250 K, 8.6 M
+//     339 -> 303; 2.4 M, 120 M 3111 -> 2567)
+//   129-256 inputs double the matrix work: up to 128 outputs on large graphs (200 -> 128:
+//     250 K, 8.9 M 271 -> 263; 2.4 M, 30 M 1500 -> 1380; 256 -> 70: 2.4 M, 12 M (five a row)
+//     1177 -> 1200; but 169 K, 2.5 M 142 -> 155); two-weight layers are at best level
+//     (1.2 M, 14 M 1097 -> 1179; 2.4 M, 120 M 3446 -> 3445); with 256 outputs codes stay
+//     ahead where they fit the last-level cache (233 K nodes: 2.4 against 2.9 ms) and
+//     are level elsewhere.
+bool sign_supported(int64_t n, int64_t nnz, int32_t d, int32_t K, bool two_weight, int leaves) {
   constexpr int64_t M = 1 << 20;
   if (d <= 64 || K > 256 || !q8_supported(n, d, K)) return false;
-  if (K > 128) return d <= 128 && nnz >= 8 * M;
-  return nnz >= (two_weight ? 8 * M : d <= 128 || fused ? 2 * M : 4 * M);
+  if (K > 128) return !two_weight && d <= 128 && nnz >= 8 * M && nnz >= 8 * n;
+  if (two_weight) return nnz >= 8 * M && nnz >= 8 * n;
+  if (d <= 128) return nnz >= 2 * M;
+  if (leaves == 4) return nnz >= (nnz >= 8 * n ? 2 : 8) * M;
+  if (leaves == 1) return (nnz >= 2 * M && nnz >= 32 * n) || (nnz >= 4 * M && nnz >= 12 * n);
+  return nnz >= 4 * M;
 }
 
 hipError_t launch_spmm_sign(int64_t n, int64_t nnz, const int64_t* rowptr,
@@ -807,7 +818,7 @@ hipError_t launch_spmm_sign(int64_t n, int64_t nnz, const int64_t* rowptr,
   FusedNext none = {};
   const FusedNext& fn = next != nullptr ? *next : none;
   // a fused next layer of products (kind 1) has at most 64 columns here
-  if (!sign_supported(n, nnz, d, K, fn.kind == 3, fn.kind == 1 || fn.kind == 4) ||
+  if (!sign_supported(n, nnz, d, K, fn.kind == 3, fn.kind == 3 ? 0 : fn.kind) ||
       (fn.kind == 1 && q8_lane_bytes(fn.d_out) != 1) ||
       (fn.kind == 4 && fn.ldFn != q8_lane_bytes(d)) ||
       (fn.kind == 3 && !self_in_epilogue_supported(nnz, d, fn.kin)))

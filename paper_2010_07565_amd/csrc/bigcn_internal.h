@@ -164,8 +164,9 @@ hipError_t launch_spmm_q8(int64_t n, int64_t nnz, const int64_t* rowptr,
 // launch_spmm_q8 on the same signs and scales, bit for bit.  F: rows of
 // sign_row_words(K) words (pad bits and words zero), g: the unflagged scales,
 // wbits [d][ldw]: this layer's packed W^T.
-// fused: its epilogue forms the next layer's input (FusedNext kind 1 or 4).
-bool sign_supported(int64_t n, int64_t nnz, int32_t d, int32_t K, bool two_weight, bool fused);
+// leaves: what its epilogue forms of the next layer's input (FusedNext kind 1 or
+// 4, or 0).
+bool sign_supported(int64_t n, int64_t nnz, int32_t d, int32_t K, bool two_weight, int leaves);
 constexpr int64_t sign_row_words(int32_t K) { return K <= 128 ? 2 : 4; }
 hipError_t launch_spmm_sign(int64_t n, int64_t nnz, const int64_t* rowptr,
                             const int32_t* colidx, int mean, const float* g,

@@ -2419,11 +2419,13 @@ bool q8_supported(int64_t n, int32_t N, int32_t K) {
 //   both: 100 -> 200 -> 200 -> 200: 2 K, 50 K 55 / 57; 5 K, 125 K 77 / 79; 5 K, 25 K 67 / 64;
 //     10 K, 250 K 99.7 / 99.1; 20 K, 500 K 166 / 156; 400 K, 1.6 M 648 / 581
 // After a narrow layer signs are faster throughout (100 -> 40 -> 256: 2 K, 10 K 34 / 28).
+// (From 2^21 entries on the layer itself may gather signs, whose epilogue has no
+// wide products.)
 bool wide_products_in_epilogue(int64_t n, int64_t nnz, int32_t d, int32_t dn) {
   constexpr int64_t few = 1 << 18;
   if (d <= 64) return false;
   const int words = q8_lane_bytes(d) * q8_lane_bytes(dn);
-  if (words <= 4) return nnz < few || nnz < 64 * n;
+  if (words <= 4) return nnz < few || (nnz < 64 * n && nnz < 8 * few);
   if (words == 8) return nnz < few && n < 16384;
   return nnz < few && n <= 6000 && nnz >= 10 * n;
 }

@@ -48,5 +48,6 @@ def gathers_signs(n, nnz, dims, layer, sage=False):
     """Whether the forward's aggregation of this layer gathers packed signs, by the
     library's own rule, for a model of these widths all of whose layers are on
     the 8-bit path."""
-    fused = not sage and layer + 2 < len(dims)
-    return bg._lib.sign_supported(n, nnz, dims[layer + 1], dims[layer], sage, fused)
+    layers = [bg.Layer(a, b, None, None, wbits_self=sage or None)
+              for a, b in zip(dims[:-1], dims[1:])]
+    return bg._lib.forward_route(n, nnz, layers)[layer]["signs"]

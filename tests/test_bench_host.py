@@ -1,13 +1,16 @@
-"""Host-side logic of bench.py (no GPU): the single-GPU guard and the lookup
-of measured HBM traffic, which must refuse counter figures taken on other
-kernel sources."""
+"""Host-side logic of bench.py (no GPU): the single-GPU guard, the lookup of measured
+HBM traffic, which must refuse counter figures taken on other kernel sources, and
+the library's rules for what a forward pass launches."""
 import hashlib
 import json
 import os
 import subprocess
 import sys
 
+import pytest
+
 import bench
+from helpers import gathers_signs
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -79,6 +82,25 @@ def test_forward_route_follows_the_library():
     route = bg._lib.forward_route(2000, 50000, layers)
     assert not any(r["signs"] for r in route)
     assert [r["leaves"] for r in route] == ["products", "products", None]
+
+
+@pytest.mark.parametrize("n,nnz,dims,sage,signs", [
+    (169_343, 2_469_343, [128, 256, 256, 40], False, True),    # leaves signs
+    (700_000, 2_900_000, [65, 192, 65], False, False), (2_400_000, 12_000_000, [65, 192, 65], False, True),
+    (169_343, 2_469_343, [100, 256, 47], False, False),        # leaves products: short rows
+    (700_000, 2_100_000, [100, 256, 47], False, False),
+    (1_200_000, 5_200_000, [100, 256, 47], False, False),
+    (2_400_000, 12_000_000, [100, 256, 47], False, False),
+    (300_000, 5_300_000, [100, 256, 47], False, True),
+    (20_000, 2_400_000, [100, 256, 47], False, True),
+    (700_000, 2_100_000, [100, 128], False, True),
+    (300_000, 3_500_000, [128, 256], False, False), (1_200_000, 5_200_000, [128, 256], False, True),
+    (250_000, 8_850_000, [200, 128], False, True), (2_400_000, 12_000_000, [256, 70], False, False),
+    (2_400_000, 9_600_000, [100, 128], True, False), (250_000, 8_600_000, [100, 128], True, True),
+    (1_200_000, 14_000_000, [200, 128], True, False)])
+def test_layers_that_gather_signs(n, nnz, dims, sage, signs):
+    """The lines of the rule at shapes measured on either side of them."""
+    assert gathers_signs(n, nnz, dims, 0, sage) == signs
 
 
 def test_committed_traffic_summaries_parse():

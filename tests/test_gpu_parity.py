@@ -1017,12 +1017,12 @@ _SIGN_GRAPHS = {}
 
 def _sign_graph(kind):
     """Graphs large enough for the aggregations over packed signs: 2^21
-    entries ("small"), 2^23 ("large"), and "holes", small with rows that have
-    no entries before, between and after the others."""
+    entries ("small"), 2^23 ("large"), and each with rows that have no entries
+    before, between and after the others ("holes", "large holes")."""
     if kind not in _SIGN_GRAPHS:
-        g = workloads.rmat_graph(*((60_000, 4_250_000, 5) if kind == "large"
+        g = workloads.rmat_graph(*((60_000, 4_250_000, 5) if kind.startswith("large")
                                    else (40_001, 1_070_000, 6)))
-        if kind == "holes":
+        if kind.endswith("holes"):
             n = 3 * g.n + 500
             deg = np.zeros(n, dtype=np.int64)
             deg[250:250 + 3 * g.n:3] = np.diff(g.rowptr)
@@ -1038,6 +1038,7 @@ def _sign_graph(kind):
     ("small", "sym", "relu", [128, 193]), ("large", "sym", "relu", [128, 193]),
     ("large", "mean", "none", [127, 193]), ("small", "mean", "none", [100, 63, 200, 5]),
     ("small", "sym", "relu", [70, 7, 96]), ("holes", "mean", "none", [100, 256, 47]),
+    ("large holes", "mean", "none", [100, 256, 47]), ("large holes", "sym", "relu", [63, 130, 9]),
     ("holes", "sym", "relu", [65, 127, 128, 65]), ("holes", "sym", "none", [100, 200, 256, 7]),
     ("large", "mean", "relu", [129, 65]),
     ("large", "sym", "none", [256, 128, 128, 40]), ("large", "mean", "none", [255, 97, 5])])
@@ -1047,11 +1048,14 @@ def test_forward_over_signs_equals_chained(dev, kind, norm, act, dims):
     points, which gather ready products.  Two feature rows have the signs of
     a weight column (the largest products)."""
     g = _sign_graph(kind)
-    # (unfused layers of 129 and more outputs take more entries than "small" has;
-    # layers of at most 64 outputs gather codes and leave signs)
+    # (layers of 129 and more outputs take more entries than "small" has, or more a
+    # row than "holes" where they leave products; layers of at most 64 outputs
+    # gather codes and leave signs)
     signs = [gathers_signs(g.n, g.nnz, dims, l) for l in range(len(dims) - 1)]
-    assert any(signs) or (kind, dims) == ("small", [128, 193])
-    assert signs[0] or dims[1] <= 64 or dims == [128, 193]
+    if (kind, dims) in (("small", [128, 193]), ("holes", [100, 256, 47])):
+        assert not any(signs)
+    else:
+        assert signs[0 if dims[1] > 64 else 1]
     rng = np.random.default_rng(sum(dims))
     L = len(dims) - 1
     x = rng.standard_normal((g.n, dims[0])).astype(np.float32)
@@ -1118,7 +1122,7 @@ def test_forward_over_signs_when_a_scale_overflows(dev, dims):
 @pytest.mark.parametrize("dims", [[100, 256, 47], [65, 65, 128], [200, 128, 9]])
 def test_sage_forward_over_signs_equals_chained(dev, dims):
     g = workloads.without_self_loops(_sign_graph("large"))
-    assert gathers_signs(g.n, g.nnz, dims, 0, sage=True)
+    assert gathers_signs(g.n, g.nnz, dims, 0, sage=True) == (dims[0] <= 128)
     rng = np.random.default_rng(sum(dims))
     L = len(dims) - 1
     xt = _t(rng.standard_normal((g.n, dims[0])).astype(np.float32), dev)
