@@ -4,10 +4,10 @@
 //   k_spmm_sign      aggregation that gathers packed signs and forms the
 //                    products itself
 //   k_bgemm_q8_e2m1  binary GEMM into 8-bit half-codes
-// Matrix and vector instructions of a SIMD do not overlap here (32 fp32 FMAs
-// and two of these products take 128 cycles, as they would one after the
-// other), so the cost of a tile is the sum of both; FMA, add and move issue
-// every 2.2 cycles with two waves, most other vector instructions every 4.3.
+// The 100 -> 256 aggregation of the products-shaped graph keeps the matrix core
+// busy for 40 % of the SIMD cycles; in 62 % of those a vector instruction issues as
+// well.  Vector instructions, at four cycles each, take 78 %, either kind 93 %: it
+// is bound by vector issue, with most of the products beside it.
 
 #include "bigcn_device.h"
 
@@ -84,11 +84,11 @@ __device__ inline float lane_float(float v, int i) {  // i wave-uniform
 // The sums of k_spmm_wave_q8 (the same chunks of edges, rows cut by a chunk
 // boundary left to k_spmm_fix_q8) with a gather of packed signs: 16 or 32
 // bytes an edge instead of the 128 or 256 of ready products, whose lines past
-// L2 bound k_spmm_wave_q8.  Here a tile of 32 edges is bound by its matrix and
-// vector instructions: for 128 inputs and 256 outputs 16 products (512
-// cycles), 128 FMAs (~300) and ~110 others (~450).  Products-shaped graph
-// (2.45 M nodes, 126 M entries), 100 -> 256: 4.31 -> 2.96 ms; 100 -> 128 layer
-// with its pack 3.08 -> 2.14 ms.  A wave takes `run` consecutive chunks.
+// L2 bound k_spmm_wave_q8.  Here a tile of 32 edges is bound by its vector
+// instructions: for 128 inputs and 256 outputs 128 FMAs and ~110 others, beside
+// 16 products of 32 cycles.  Products-shaped graph (2.45 M nodes, 126 M entries),
+// 100 -> 256: 4.31 -> 2.90 ms, 0.45 lines an edge past L2 instead of 1.9; 100 -> 128
+// layer with its pack 3.08 -> 2.14 ms.  A wave takes `run` consecutive chunks.
 //
 // A wave works through a chunk in tiles of four blocks of eight edges.  A
 // block holds edges of one row only (the first block of a row starts at the
@@ -112,7 +112,7 @@ __device__ inline float lane_float(float v, int i) {  // i wave-uniform
 // once per window.
 //
 // The layer's weights are read from LDS at every product (in registers they
-// left two waves per SIMD: 3.3 instead of 2.96 ms), at three waves per SIMD
+// left two waves per SIMD and 0.3 ms more there), at three waves per SIMD
 // half of the LDS rate.
 //
 // ID: the products are the signs themselves (the weights are the identity,
