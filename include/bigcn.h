@@ -363,10 +363,11 @@ bigcn_status bigcn_source_slots(int64_t n, int64_t nnz, const int64_t* rowptr,
  * Internally each layer's products are kept exactly: as 8-bit half-codes
  * (see bigcn_bgemm_q8) for layers of up to 256 output columns with
  * d_in <= 2048, otherwise in IEEE half (d_in <= 2048) or int16.  When two
- * consecutive layers both use 8-bit codes, the second layer's sign pack and
- * binary GEMM run inside the aggregation that produces its input: the
- * hidden activations are not written to memory unless the layer gives an
- * output (bigcn_layer.out).  The result is
+ * consecutive layers both use 8-bit codes, the second layer's sign pack, and
+ * its binary GEMM where that is faster, run inside the aggregation that
+ * produces its input: the hidden activations are not written to memory unless
+ * the layer gives an output (bigcn_layer.out).  Wide layers of large graphs
+ * gather packed signs and form their products while aggregating.  The result is
  * bit-identical to chaining the per-step entry points (bigcn_binarize_pack,
  * bigcn_bgemm_q8, bigcn_spmm_csr_q8 for 8-bit layers).
  * A layer with wbits_self set is a two-weight GraphSAGE layer: the graph
